@@ -10,14 +10,14 @@
 //     the kernel's job is to keep enough 128-bit loads in flight and to spend
 //     as few instructions as possible outside the per-pixel loop.
 //   * A wave of 64 lanes is cut into groups of seg*rp lanes, one group per
-//     tile: `seg` lanes stream along a tile row (seg*vec floats wide) and `rp`
-//     such segments take interleaved rows.  So a wave covers 64/(seg*rp)
-//     adjacent tiles, and a whole tile slice reduces inside one wave with DPP
-//     lane permutations, with no LDS and no barrier.  Several waves of a
-//     workgroup may share a tile's rows (combined once in LDS), and for shapes
-//     with few large tiles several workgroups share them (the last of them to
-//     finish combines their partials, chosen by an atomic ticket; no second
-//     launch).
+//     tile, which read the tile's rows in 16-byte quads: short tile rows a few
+//     at a time, long ones quad by quad in turn (see slice_sums).  So a wave
+//     covers 64/(seg*rp) adjacent tiles, and a whole tile slice reduces inside
+//     one wave with DPP lane permutations, with no LDS and no barrier.  Several
+//     waves of a workgroup may share a tile's rows (combined once in LDS), and
+//     for shapes with few large tiles several workgroups share them (the last
+//     of them to finish combines their partials, chosen by an atomic ticket; no
+//     second launch).
 //   * Each lane folds `vec` adjacent pixels with plain FP32 (FMA chains) and
 //     adds the block into Kahan-compensated (hi, lo) accumulators: the long
 //     per-lane sums are compensated.  Across lanes the partial sums are folded
@@ -40,6 +40,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -53,29 +54,41 @@ enum Mode : int { kLisi = 1, kAug = 2, kBoth = 3 };
 // How the parts of a split tile group are added up (see split_finish).
 enum SplitMode : int { kSplitNone = 0, kSplitTicket = 1, kSplitCombine = 2 };
 
-struct KArgs {
+// One pair's work (also a batch descriptor's payload): see slice_sums for the
+// geometry fields.
+struct PairArgs {
     const float *x;
     const float *y;
-    int32_t N;           // image side (row stride in floats), <= 2^17
-    int32_t smode;       // split tiles: kSplitNone, kSplitTicket or kSplitCombine
-    int32_t NT;          // tile side
-    int32_t ns;          // tiles per side
-    int32_t ngx;         // tile groups along x: ceil(ns / ht)
-    int32_t log_seg;     // log2(lanes per segment)
-    int32_t log_grp;     // log2(lanes per tile in a wave) = log2(seg * rp)
-    int32_t ht;          // tiles per wave: 64 / (seg * rp)
-    int32_t ks;          // workgroups per tile group
-    int32_t rows_wave;   // tile rows per wave slice: NT / (waves * ks)
-    int32_t lpt;         // column groups per tile row: NT / vec
-    int32_t cpl;         // column chunks per lane: ceil(lpt / seg)
-    uint32_t ngx_m;      // division multipliers for ngx and ks (see udiv)
-    uint32_t ks_m;
-    float D, C1, C2, C;
     float *lisi;
     float *aug;
     float *sums;
+    float D, C1, C2, C;
+    int32_t N;           // image side (row stride in floats), <= 2^17
+    int32_t NT;          // tile side
+    int32_t ns;          // tiles per side
+    int32_t ngx;         // tile groups along x: ceil(ns / ht)
+    uint32_t ngx_m;      // division multiplier for ngx (see udiv)
+    int32_t log_grp;     // log2(G), lanes per tile in a wave; ht = 64 / G tiles per wave
+    int32_t rows_wave;   // tile rows per wave slice: NT / (waves * ks)
+    int32_t cols;        // quads (VEC pixels) per tile row: ceil(NT / vec)
+    int32_t pitch;       // quad places per tile row that the lanes count with
+    uint32_t pitch_m;    // ceil(2^31 / pitch)
+    int32_t lead;        // lead_rows * pitch - shift
+    int32_t lead_rows;   // rows above the slice that lane 0 starts counting from
+    int32_t step;        // bytes from one of a lane's items to the next, before a wrap
+    int64_t items;       // loads per lane and image: ceil(rows_wave * pitch / G)
+};
+
+struct KArgs : PairArgs {
+    int32_t smode;       // split tiles: kSplitNone, kSplitTicket or kSplitCombine
+    int32_t ks;          // workgroups per tile group
+    uint32_t ks_m;       // division multiplier for ks
     float *ws;           // split partials: [group][ks][ht][4]
 };
+
+__host__ __device__ __forceinline__ int tiles_per_wave(const PairArgs &a) {
+    return 64 >> a.log_grp;
+}
 
 // ---------------------------------------------------------------------------
 // Compensated FP32 arithmetic
@@ -235,27 +248,34 @@ template <> struct VecT<1> { using T = float; };
 
 // Streaming loads: every input byte is read exactly once, so they carry the
 // nontemporal hint and do not displace other data in the caches.
-template <int VEC>
-__device__ __forceinline__ typename VecT<VEC>::T vload(const float *p) {
-    if constexpr (VEC == 4) {
+//
+// The pointer is cast to the global address space: pointers that come out of a
+// batch descriptor in memory are not known to be global, and a flat load
+// checks the LDS aperture and counts on both wait counters.  ANY: a quad at any
+// float address (the hardware takes a 16-byte global load at 4-byte alignment).
+#define IQA_GLOBAL __attribute__((address_space(1)))
+
+template <int VEC, bool ANY = false>
+__device__ __forceinline__ typename VecT<VEC>::T vload(const IQA_GLOBAL char *p) {
+    if constexpr (VEC == 4 && ANY) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+        const f4 v = __builtin_nontemporal_load(reinterpret_cast<const IQA_GLOBAL f4 *>(p));
+        return float4{v.x, v.y, v.z, v.w};
+    } else if constexpr (VEC == 4) {
         typedef float f4 __attribute__((ext_vector_type(4)));
-        const f4 v = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p));
+        const f4 v = __builtin_nontemporal_load(reinterpret_cast<const IQA_GLOBAL f4 *>(p));
         return float4{v.x, v.y, v.z, v.w};
     } else if constexpr (VEC == 2) {
         typedef float f2 __attribute__((ext_vector_type(2)));
-        const f2 v = __builtin_nontemporal_load(reinterpret_cast<const f2 *>(p));
+        const f2 v = __builtin_nontemporal_load(reinterpret_cast<const IQA_GLOBAL f2 *>(p));
         return float2{v.x, v.y};
     } else {
-        return __builtin_nontemporal_load(p);
+        return __builtin_nontemporal_load(reinterpret_cast<const IQA_GLOBAL float *>(p));
     }
 }
 
-// Load at a wave-uniform base plus a 32-bit per-lane byte offset, which the
-// hardware adds itself (no 64-bit address arithmetic per load).
-template <int VEC>
-__device__ __forceinline__ typename VecT<VEC>::T vload_off(const float *base, uint32_t byte_off) {
-    return vload<VEC>(reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) +
-                                                      byte_off));
+__device__ __forceinline__ const IQA_GLOBAL char *global_bytes(const float *p) {
+    return reinterpret_cast<const IQA_GLOBAL char *>(reinterpret_cast<uintptr_t>(p));
 }
 
 template <int VEC>
@@ -275,16 +295,19 @@ __device__ __forceinline__ float velem(const typename VecT<VEC>::T &v, int e) {
 }
 
 // Per-pixel terms of VEC adjacent pixel pairs, added with plain FP32 (FMA
-// chains) into a short block sum b.  A pair of zeros adds nothing.
-template <int VEC, int MODE>
+// chains) into a short block sum b.  A pair of zeros adds nothing.  SKIP: the
+// first `skip` elements are not counted (the clamp's threshold is infinite).
+template <int VEC, int MODE, bool SKIP = false>
 __device__ __forceinline__ void accumulate(const typename VecT<VEC>::T &xv,
-                                           const typename VecT<VEC>::T &yv, float C1, Sum4 &b) {
+                                           const typename VecT<VEC>::T &yv, float C1, Sum4 &b,
+                                           int skip = 0) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         const float xr = velem<VEC>(xv, e);
         const float yr = velem<VEC>(yv, e);
-        const float xc = xr > 0.f ? xr : 0.f;   // Sec. 2 clamp; NaN and -0 -> +0
-        const float yc = yr > 0.f ? yr : 0.f;
+        const float floor = SKIP && e < skip ? __builtin_inff() : 0.f;
+        const float xc = xr > floor ? xr : 0.f;   // Sec. 2 clamp; NaN and -0 -> +0
+        const float yc = yr > floor ? yr : 0.f;
         const float s = xc + yc;                // |x'+y'| (both non-negative)
         const float d = fabsf(xc - yc);         // |x'-y'|
         if constexpr ((MODE & kLisi) != 0) {
@@ -314,14 +337,14 @@ __device__ __forceinline__ void add_block(Acc &acc, const Sum4 &b) {
 // compensation in before the cross-lane adds.
 
 // Eq. 1.
-__device__ __forceinline__ void finalize_lisi(const KArgs &a, int64_t t, const Sum4 &s) {
+__device__ __forceinline__ void finalize_lisi(const PairArgs &a, int64_t t, const Sum4 &s) {
     if (!a.lisi) return;
     const float den = fmaxf(s.X, s.Y) + a.C2;
     a.lisi[t] = div_pos(a.D * s.A, den, __builtin_amdgcn_rcpf(den));
 }
 
 // Eq. 2: S = Sx + Sy + C and q = P / S in double-float, then 1 - q.
-__device__ __forceinline__ void finalize_aug(const KArgs &a, int64_t t, const Sum4 &s) {
+__device__ __forceinline__ void finalize_aug(const PairArgs &a, int64_t t, const Sum4 &s) {
     if (!a.aug) return;
     float s1, e1;
     two_sum(s.X, s.Y, s1, e1);
@@ -339,12 +362,12 @@ __device__ __forceinline__ void finalize_aug(const KArgs &a, int64_t t, const Su
     a.aug[t] = h + (e - q2);
 }
 
-__device__ __forceinline__ void store_sums(const KArgs &a, int64_t t, const Sum4 &s) {
+__device__ __forceinline__ void store_sums(const PairArgs &a, int64_t t, const Sum4 &s) {
     if (a.sums) reinterpret_cast<float4 *>(a.sums)[t] = float4{s.A, s.P, s.X, s.Y};
 }
 
 template <int MODE>
-__device__ __forceinline__ void finalize(const KArgs &a, int64_t t, const Sum4 &s) {
+__device__ __forceinline__ void finalize(const PairArgs &a, int64_t t, const Sum4 &s) {
     if constexpr ((MODE & kLisi) != 0) finalize_lisi(a, t, s);
     if constexpr ((MODE & kAug) != 0) finalize_aug(a, t, s);
     if constexpr (MODE == kBoth) store_sums(a, t, s);
@@ -394,131 +417,150 @@ __device__ __forceinline__ uint64_t stamp_after(float v) {
 // One wave's slice of one tile group
 // ---------------------------------------------------------------------------
 //
-// A tile group is the ht = 64/(seg*rp) horizontally adjacent tiles one wave
-// covers: tiles txg*ht .. txg*ht+ht-1 of tile row ty.  A slice is rows
-// slice*rows_wave .. (slice+1)*rows_wave-1 of those tiles.  Lane L works on
-// tile j = L >> log_grp, row phase k = (L >> log_seg) & (rp-1) and column
-// group l = L & (seg-1): rows k, k+rp, k+2rp, ... of the slice.  Returns the
-// slice's sums of tile j, the same on every lane of the tile's lane group.
-template <int VEC, int U, int MODE, bool WIDE, bool TL = false>
-__device__ __forceinline__ Sum4 slice_sums(const KArgs &a, int ty, int txg, int slice, int lane,
+// A tile group is the ht = 64/G horizontally adjacent tiles one wave covers:
+// tiles txg*ht .. txg*ht+ht-1 of tile row ty.  A slice is rows
+// slice*rows_wave .. (slice+1)*rows_wave-1 of those tiles.  Lane L belongs to
+// tile j = L / G of the group.  A tile row is `cols` quads of VEC pixels, on
+// `pitch` places; the tile's part of the slice is rows_wave * pitch places
+// counted row by row, and the G lanes of a tile take them in turn: lane q has
+// places q - shift, q - shift + G, ..., with shift chosen so that the last item
+// of every lane exists and only the first may fall before the slice.  Returns
+// the slice's sums of tile j, the same on every lane of the tile's lane group.
+//
+// Rows of at most G quads have a pitch of the next power of two: a lane keeps
+// its column (lanes past `cols` idle) and takes every (G/pitch)-th row, at a
+// constant 32-bit step from scalar bases (a slice spans at most 256 rows, below
+// 2^28 bytes).  WRAP, longer rows: pitch == cols, so all lanes always work; a
+// lane moves G quads on from item to item, and to the next row where that
+// leaves its row.  (Counting short rows without gaps too keeps every lane busy
+// but cuts each load instruction into more pieces: measured on a mix of tile
+// sides from 12 to 100, 2 to 17% slower, e.g. 2000^2/50 9.2 against 7.9 us.
+// For wide rows it is what keeps a 300-pixel row, 75 quads, from taking two
+// loads: 3000^2/300 15.7 against 17.0 us.)
+//
+// Items are read in batches of U with the next batch in flight while the
+// current one is reduced; each batch is one block of plain FP32 sums
+// (compensation is per batch).  Items beyond a multiple of U form a batch of
+// their own that goes first, so every load has others in flight with it; the
+// item that some lanes lack is always in it.
+//
+// ANY (VEC 4): images at any float address and any NT >= 4.  A lane loads a
+// quad wherever it lies; the last quad of a tile row is moved back to end with
+// the row, and the pixels it then shares with its neighbour are not counted.
+template <int VEC, bool ANY, int U, int MODE, bool WRAP, bool TL = false>
+__device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, int slice, int lane,
                                            uint64_t *ts = nullptr) {
     using V = typename VecT<VEC>::T;
-    const int seg = 1 << a.log_seg;
-    const int log_rp = a.log_grp - a.log_seg;
-    const int rp = 1 << log_rp;
-    const int l = lane & (seg - 1);
-    const int k = (lane >> a.log_seg) & (rp - 1);
+    const int G = 1 << a.log_grp;
+    const int q = lane & (G - 1);
+    const int tx0 = txg * tiles_per_wave(a);
     const int j = lane >> a.log_grp;
-    const int tx = txg * a.ht + j;
-
-    int M = 0;   // rows of the tile this lane reduces: ceil((rows_wave - k) / rp)
-    if (tx < a.ns && k < a.rows_wave) M = (a.rows_wave - k + rp - 1) >> log_rp;
-    const int64_t col0 = (int64_t)tx * a.NT;
-    // First row of the slice: uniform across the wave, so the image pointers
-    // below live in scalar registers.
-    const int64_t srow = (int64_t)ty * a.NT + (int64_t)slice * a.rows_wave;
 
     Acc acc = acc_zero();
-
-    if constexpr (!WIDE) {
-        // One column group per lane (lanes past the tile row idle).  The slice
-        // spans rows_wave * N floats, which the host keeps below 2^30, so byte
-        // offsets from the slice start fit in 32 bits.
-        if (l >= a.lpt) M = 0;
-        const float *bx = a.x + srow * a.N;
-        const float *by = a.y + srow * a.N;
-        uint32_t off = (uint32_t)(((int64_t)k * a.N + col0 + (int64_t)l * VEC) * 4);
-        const uint32_t step = (uint32_t)((int64_t)rp * a.N * 4);
-        // Full batches of U rows, double-buffered: the next batch is in flight
-        // while this one is reduced.  Compensation is per batch.
-        int m = 0;
-        if (M >= U) {
-            V ax[U], ay[U], cx[U], cy[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                ax[u] = vload_off<VEC>(bx, off + u * step);
-                ay[u] = vload_off<VEC>(by, off + u * step);
-            }
-            off += U * step;
-            while (true) {
-                const bool more_c = m + 2 * U <= M;
-                if (more_c) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        cx[u] = vload_off<VEC>(bx, off + u * step);
-                        cy[u] = vload_off<VEC>(by, off + u * step);
-                    }
-                    off += U * step;
-                }
-                {
-                    Sum4 b{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int u = 0; u < U; ++u) accumulate<VEC, MODE>(ax[u], ay[u], a.C1, b);
-                    add_block<MODE>(acc, b);
-                    if constexpr (TL) {
-                        if (m == 0) ts[0] = stamp_after(acc.X.hi);
-                    }
-                }
-                m += U;
-                if (!more_c) break;
-                const bool more_a = m + 2 * U <= M;
-                if (more_a) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        ax[u] = vload_off<VEC>(bx, off + u * step);
-                        ay[u] = vload_off<VEC>(by, off + u * step);
-                    }
-                    off += U * step;
-                }
-                {
-                    Sum4 b{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int u = 0; u < U; ++u) accumulate<VEC, MODE>(cx[u], cy[u], a.C1, b);
-                    add_block<MODE>(acc, b);
-                }
-                m += U;
-                if (!more_a) break;
-            }
+    // Row and column of the lane's first item, counted from lead_rows above
+    // the slice (f * pitch < 2^31: the quotient is exact).
+    const uint32_t f = (uint32_t)(q + a.lead);
+    const int r = (int)__umulhi(f << 1, a.pitch_m);
+    int col = (int)f - r * a.pitch;
+    if (tx0 + j < a.ns && (WRAP || col < a.cols)) {
+        const int shift = a.lead_rows * a.pitch - a.lead;
+        const bool has_first = q >= shift;
+        // The slice's first pixel, at most 2^17 rows of at most 2^17 pixels
+        // down; the bases of lanes without a first item may lie above the image.
+        const uint32_t row0 = (uint32_t)(ty * a.NT + slice * a.rows_wave);
+        const uint64_t first = (uint64_t)row0 * (uint32_t)a.N + (uint32_t)(tx0 * a.NT);
+        const int64_t base = (int64_t)first * 4 - (int64_t)((uint32_t)(a.lead_rows * a.N) * 4u);
+        const IQA_GLOBAL char *bx = global_bytes(a.x) + base;
+        const IQA_GLOBAL char *by = global_bytes(a.y) + base;
+        const int over = a.cols * VEC - a.NT;   // ANY: pixels the last quad moves back
+        uint32_t off = (uint32_t)(r * a.N + j * a.NT + col * VEC) * 4u;
+        int skip = 0;                          // ANY without WRAP: pixels not counted
+        if constexpr (ANY && !WRAP) {
+            skip = col == a.cols - 1 ? over : 0;
+            off -= (uint32_t)skip * 4u;
         }
-        // Remaining rows (fewer than U), one at a time.
-        for (; m < M; ++m) {
-            const V xv = vload_off<VEC>(bx, off);
-            const V yv = vload_off<VEC>(by, off);
-            off += step;
+        if constexpr (WRAP) {   // the lanes move apart: per-lane addresses
+            bx += off;
+            by += off;
+            off = 0;
+        }
+        const int64_t wrap_step = (int64_t)a.step + (int64_t)a.N * 4 - (int64_t)a.cols * (VEC * 4);
+        auto load_item = [&](V &xv, V &yv, bool ok, int u, uint32_t &last) {
+            int back = 0;
+            if constexpr (ANY && WRAP) {
+                const bool end = col == a.cols - 1;
+                back = end ? over * 4 : 0;
+                last |= end ? 1u << u : 0u;
+            }
+            if (ok) {
+                xv = vload<VEC, ANY>(bx + off - back);
+                yv = vload<VEC, ANY>(by + off - back);
+            } else {
+                xv = vzero<VEC>();
+                yv = vzero<VEC>();
+            }
+            if constexpr (WRAP) {
+                col += G;
+                const bool wrap = col >= a.cols;
+                col -= wrap ? a.cols : 0;
+                bx += wrap ? wrap_step : a.step;
+                by += wrap ? wrap_step : a.step;
+            } else {
+                off += (uint32_t)a.step;
+            }
+        };
+        auto load = [&](V (&xv)[U], V (&yv)[U], uint32_t &last) {
+            last = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) load_item(xv[u], yv[u], true, u, last);
+        };
+        auto reduce_item = [&](const V &xv, const V &yv, int u, uint32_t last, Sum4 &b) {
+            int sk = skip;
+            if constexpr (ANY && WRAP) sk = (last >> u) & 1 ? over : 0;
+            accumulate<VEC, MODE, ANY>(xv, yv, a.C1, b, sk);
+        };
+        auto reduce = [&](const V (&xv)[U], const V (&yv)[U], uint32_t last) {
             Sum4 b{0.f, 0.f, 0.f, 0.f};
-            accumulate<VEC, MODE>(xv, yv, a.C1, b);
+#pragma unroll
+            for (int u = 0; u < U; ++u) reduce_item(xv[u], yv[u], u, last, b);
             add_block<MODE>(acc, b);
-            if constexpr (TL) {
-                if (m == 0) ts[0] = stamp_after(acc.X.hi);
-            }
+        };
+        // Full batches, and the items of the partial one (0..U).
+        using Count = std::conditional_t<WRAP, uint64_t, uint32_t>;
+        const Count n = (Count)a.items;
+        Count left = (n - (shift ? 1 : 0)) / U;
+        const int part = (int)(n - left * U);
+
+        V ax[U], ay[U], cx[U], cy[U];
+        uint32_t alast = 0, clast = 0;
+        if (part) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u < part) load_item(cx[u], cy[u], u > 0 || has_first, u, clast);
         }
-    } else {
-        // Tile rows wider than a segment: chunk q covers column group l + q*seg.
-        for (int m = 0; m < M; ++m) {
-            const int64_t row = srow + k + (int64_t)m * rp;
-            const float *px = a.x + row * a.N + col0;
-            const float *py = a.y + row * a.N + col0;
-            for (int q0 = 0; q0 < a.cpl; q0 += U) {
-                V xv[U], yv[U];
+        if (left) load(ax, ay, alast);
+        if (part) {
+            Sum4 b{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int cg = l + (q0 + u) * seg;
-                    if (q0 + u < a.cpl && cg < a.lpt) {
-                        xv[u] = vload<VEC>(px + (int64_t)cg * VEC);
-                        yv[u] = vload<VEC>(py + (int64_t)cg * VEC);
-                    } else {
-                        xv[u] = vzero<VEC>();
-                        yv[u] = vzero<VEC>();
-                    }
-                }
-                Sum4 b{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int u = 0; u < U; ++u) accumulate<VEC, MODE>(xv[u], yv[u], a.C1, b);
-                add_block<MODE>(acc, b);
+            for (int u = 0; u < U; ++u)
+                if (u < part) reduce_item(cx[u], cy[u], u, clast, b);
+            add_block<MODE>(acc, b);
+            if constexpr (TL) ts[0] = stamp_after(acc.X.hi);
+        }
+        if (left) {
+            while (true) {
+                const bool more_c = left > 1;
+                if (more_c) load(cx, cy, clast);
+                reduce(ax, ay, alast);
                 if constexpr (TL) {
-                    if (m == 0 && q0 == 0) ts[0] = stamp_after(acc.X.hi);
+                    if (ts[0] == 0) ts[0] = stamp_after(acc.X.hi);
                 }
+                if (!more_c) break;
+                const bool more_a = left > 2;
+                if (more_a) load(ax, ay, alast);
+                reduce(cx, cy, clast);
+                if (!more_a) break;
+                left -= 2;
             }
         }
     }
@@ -622,11 +664,12 @@ __device__ __forceinline__ void combine_parts(const KArgs &a, int grp, int lane)
     const int g = 1 << a.log_grp;
     const int j = lane >> a.log_grp;
     const int q = lane & (g - 1);
-    const int tx = txg * a.ht + j;
+    const int ht = tiles_per_wave(a);
+    const int tx = txg * ht + j;
     Acc c = acc_zero();
     if (tx < a.ns) {
         for (int p = q; p < a.ks; p += g) {
-            const float4 *src = ws + (base + p) * a.ht + j;
+            const float4 *src = ws + (base + p) * ht + j;
             const float4 w = COHERENT ? load_coherent(src) : *src;
             if constexpr ((MODE & kLisi) != 0) cadd(c.A, w.x);
             if constexpr ((MODE & kAug) != 0) cadd(c.P, w.y);
@@ -644,7 +687,7 @@ template <int MODE>
 __device__ __forceinline__ bool split_finish(const KArgs &a, int grp, int part, int lane, bool mine,
                                              int jt, float4 v) {
     float4 *ws = reinterpret_cast<float4 *>(a.ws);
-    float4 *slot = ws + ((int64_t)grp * a.ks + part) * a.ht + jt;
+    float4 *slot = ws + ((int64_t)grp * a.ks + part) * tiles_per_wave(a) + jt;
     if (a.smode == kSplitCombine) {
         if (mine) *slot = v;
         return false;
@@ -684,7 +727,7 @@ __device__ __forceinline__ bool split_finish(const KArgs &a, int grp, int part, 
 // plus the XCD and hardware slot it ran on: 8 uint64 per workgroup at
 // tl[8 * blockIdx.x], written with ordinary vector stores; the split part's
 // word has bit 32 set when this workgroup finished its tiles.
-template <int VEC, int WAVES, int U, int MODE, bool WIDE, bool SPLIT, bool TL>
+template <int VEC, bool ANY, int WAVES, int U, int MODE, bool WRAP, bool SPLIT, bool TL>
 __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     uint64_t ts[4] = {0, 0, 0, 0};
     if constexpr (TL) ts[0] = wall_clock64();
@@ -695,8 +738,9 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     const int part = bid - grp * a.ks;
     const int ty = udiv(grp, a.ngx_m, a.ngx);
     const int txg = grp - ty * a.ngx;
+    const int ht = tiles_per_wave(a);
 
-    const Sum4 s = slice_sums<VEC, U, MODE, WIDE, TL>(a, ty, txg, part * WAVES + wave, lane, ts + 1);
+    const Sum4 s = slice_sums<VEC, ANY, U, MODE, WRAP, TL>(a, ty, txg, part * WAVES + wave, lane, ts + 1);
     constexpr bool kTwoWaveFinish = WAVES > 1 && MODE == kBoth && !SPLIT;
 
     // The tile this lane finishes, if any: a lane group's leader with one wave
@@ -706,7 +750,7 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     float4 v{s.A, s.P, s.X, s.Y};
     if constexpr (WAVES == 1) {
         jt = lane >> a.log_grp;
-        mine = (lane & ((1 << a.log_grp) - 1)) == 0 && txg * a.ht + jt < a.ns;
+        mine = (lane & ((1 << a.log_grp) - 1)) == 0 && txg * ht + jt < a.ns;
     } else {
         // Combine the waves' slices of each tile in LDS, wave order fixed.
         __shared__ float4 lds[WAVES][kWave];
@@ -714,7 +758,7 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
         __syncthreads();
         if (wave != 0 && !(kTwoWaveFinish && wave == 1)) return;
         jt = lane;
-        mine = lane < a.ht && txg * a.ht + lane < a.ns;
+        mine = lane < ht && txg * ht + lane < a.ns;
         if (mine) {
             float4 w[WAVES];
 #pragma unroll
@@ -724,7 +768,7 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     }
     bool last = true;   // this workgroup finished its tiles
     if constexpr (!SPLIT) {
-        const int64_t t = (int64_t)ty * a.ns + txg * a.ht + jt;
+        const int64_t t = (int64_t)ty * a.ns + txg * ht + jt;
         const Sum4 r{v.x, v.y, v.z, v.w};
         if constexpr (kTwoWaveFinish) {
             if (mine && wave == 0) {
@@ -757,14 +801,14 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     }
 }
 
-template <int VEC, int WAVES, int U, int MODE, bool WIDE, bool SPLIT>
+template <int VEC, bool ANY, int WAVES, int U, int MODE, bool WRAP, bool SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void tiles_kernel(KArgs a) {
-    tiles_body<VEC, WAVES, U, MODE, WIDE, SPLIT, false>(a, nullptr);
+    tiles_body<VEC, ANY, WAVES, U, MODE, WRAP, SPLIT, false>(a, nullptr);
 }
 
-template <int VEC, int WAVES, int U, bool WIDE, bool SPLIT>
+template <int VEC, int WAVES, int U, bool WRAP, bool SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void tiles_kernel_tl(KArgs a, uint64_t *tl) {
-    tiles_body<VEC, WAVES, U, kBoth, WIDE, SPLIT, true>(a, tl);
+    tiles_body<VEC, false, WAVES, U, kBoth, WRAP, SPLIT, true>(a, tl);
 }
 
 // kSplitCombine: one wave per tile group adds its parts, after the tile
@@ -791,7 +835,7 @@ __global__ __launch_bounds__(kWave) void combine_kernel(KArgs a) {
 // results are bitwise equal to a single-pair launch with the same geometry
 // and unroll (ksplit 1).
 struct BatchDesc {
-    KArgs a;
+    PairArgs a;
     int64_t unit_begin;
 };
 static_assert(sizeof(BatchDesc) <= IQA_BATCH_DESC_BYTES, "batch descriptor size");
@@ -799,10 +843,15 @@ static_assert(sizeof(BatchDesc) <= IQA_BATCH_DESC_BYTES, "batch descriptor size"
 constexpr int kBatchWaves = 4;   // waves per workgroup
 
 // A pair whose waves split its tile groups' rows (rows_wave < NT).
-__host__ __device__ __forceinline__ bool batch_coop(const KArgs &a) { return a.rows_wave != a.NT; }
+__host__ __device__ __forceinline__ bool batch_coop(const PairArgs &a) { return a.rows_wave != a.NT; }
+
+// A pair whose tile rows are longer than a tile's lanes.
+__host__ __device__ __forceinline__ bool batch_wrap(const PairArgs &a) {
+    return a.cols > 1 << a.log_grp;
+}
 
 // Work units of one pair.
-__host__ __device__ __forceinline__ int64_t batch_units(const KArgs &a) {
+__host__ __device__ __forceinline__ int64_t batch_units(const PairArgs &a) {
     const int64_t groups = (int64_t)a.ns * a.ngx;
     return batch_coop(a) ? groups : (groups + kBatchWaves - 1) / kBatchWaves;
 }
@@ -820,7 +869,7 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
             if (descs[mid].unit_begin <= u) lo = mid; else hi = mid - 1;
         }
         const int pi = __builtin_amdgcn_readfirstlane(lo);
-        const KArgs a = descs[pi].a;
+        const PairArgs a = descs[pi].a;
         // A unit outside the pair's units (a unit count or pair count that
         // does not match the table) is skipped, never read.
         const int64_t g64 = u - descs[pi].unit_begin;
@@ -832,22 +881,23 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
             const int grp = (int)grp64;
             const int ty = udiv(grp, a.ngx_m, a.ngx);
             const int txg = grp - ty * a.ngx;
-            const Sum4 s = a.cpl > 1 ? slice_sums<4, U, kBoth, true>(a, ty, txg, 0, lane)
-                                     : slice_sums<4, U, kBoth, false>(a, ty, txg, 0, lane);
-            const int tx = txg * a.ht + (lane >> a.log_grp);
+            const Sum4 s = batch_wrap(a) ? slice_sums<4, false, U, kBoth, true>(a, ty, txg, 0, lane)
+                                     : slice_sums<4, false, U, kBoth, false>(a, ty, txg, 0, lane);
+            const int tx = txg * tiles_per_wave(a) + (lane >> a.log_grp);
             if (leader && tx < a.ns) finalize<kBoth>(a, (int64_t)ty * a.ns + tx, s);
         } else {
             // Workgroup-uniform branch: every wave reaches both barriers.
             const int grp = (int)g64;
             const int ty = udiv(grp, a.ngx_m, a.ngx);
             const int txg = grp - ty * a.ngx;
-            const Sum4 s = a.cpl > 1 ? slice_sums<4, U, kBoth, true>(a, ty, txg, wave, lane)
-                                     : slice_sums<4, U, kBoth, false>(a, ty, txg, wave, lane);
+            const Sum4 s = batch_wrap(a) ? slice_sums<4, false, U, kBoth, true>(a, ty, txg, wave, lane)
+                                     : slice_sums<4, false, U, kBoth, false>(a, ty, txg, wave, lane);
             if (leader) lds[wave][lane >> a.log_grp] = float4{s.A, s.P, s.X, s.Y};
             __syncthreads();
             // Two waves finish the tiles at once, as in the tile kernel.
-            if (wave < 2 && lane < a.ht) {
-                const int txl = txg * a.ht + lane;
+            const int ht = tiles_per_wave(a);
+            if (wave < 2 && lane < ht) {
+                const int txl = txg * ht + lane;
                 if (txl < a.ns) {
                     float4 v[kBatchWaves];
 #pragma unroll
@@ -937,7 +987,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs m) {
     const float4 a = part[0], b = part[1], c = part[2], d = part[3];
     const Sum4 t{(a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y),
                  (a.z + b.z) + (c.z + d.z), (a.w + b.w) + (c.w + d.w)};
-    KArgs k{};
+    PairArgs k{};
     k.D = m.D;
     k.C2 = m.C2;
     k.C = m.C;
@@ -962,15 +1012,15 @@ __global__ __launch_bounds__(256) void read_ceiling_kernel(const float4 *__restr
     const int64_t b1 = b0 + per_block < n4 ? b0 + per_block : n4;
     float acc = 0.f;
     int64_t i = b0 + threadIdx.x;
-    const float *f = reinterpret_cast<const float *>(src);
+    const IQA_GLOBAL char *f = global_bytes(reinterpret_cast<const float *>(src));
     for (; i + 3 * 256 < b1; i += 4 * 256) {
-        const float4 a = vload<4>(f + 4 * i), b = vload<4>(f + 4 * (i + 256));
-        const float4 c = vload<4>(f + 4 * (i + 512)), d = vload<4>(f + 4 * (i + 768));
+        const float4 a = vload<4>(f + 16 * i), b = vload<4>(f + 16 * (i + 256));
+        const float4 c = vload<4>(f + 16 * (i + 512)), d = vload<4>(f + 16 * (i + 768));
         acc += (a.x + a.y + a.z + a.w) + (b.x + b.y + b.z + b.w) +
                (c.x + c.y + c.z + c.w) + (d.x + d.y + d.z + d.w);
     }
     for (; i < b1; i += 256) {
-        const float4 a = vload<4>(f + 4 * i);
+        const float4 a = vload<4>(f + 16 * i);
         acc += a.x + a.y + a.z + a.w;
     }
     for (int st = 32; st > 0; st >>= 1) acc += __shfl_xor(acc, st, kWave);
@@ -1010,74 +1060,79 @@ iqa_status hip_status(hipError_t e) {
 
 using LaunchFn = hipError_t (*)(const KArgs &, uint64_t *, unsigned, hipStream_t);
 
-template <int VEC, int WAVES, int U, int MODE, bool WIDE, bool SPLIT>
+template <int VEC, bool ANY, int WAVES, int U, int MODE, bool WRAP, bool SPLIT>
 hipError_t launch_impl(const KArgs &a, uint64_t *, unsigned grid, hipStream_t s) {
-    return launch_kernel(&tiles_kernel<VEC, WAVES, U, MODE, WIDE, SPLIT>, grid, WAVES * kWave, s,
-                         a);
+    return launch_kernel(&tiles_kernel<VEC, ANY, WAVES, U, MODE, WRAP, SPLIT>, grid,
+                         WAVES * kWave, s, a);
 }
 
-template <int VEC, int WAVES, int U, bool WIDE, bool SPLIT>
+template <int VEC, int WAVES, int U, bool WRAP, bool SPLIT>
 hipError_t launch_tl(const KArgs &a, uint64_t *tl, unsigned grid, hipStream_t s) {
-    return launch_kernel(&tiles_kernel_tl<VEC, WAVES, U, WIDE, SPLIT>, grid, WAVES * kWave, s, a,
+    return launch_kernel(&tiles_kernel_tl<VEC, WAVES, U, WRAP, SPLIT>, grid, WAVES * kWave, s, a,
                          tl);
 }
 
 // What a launch needs, mapped onto the instantiated kernels.
 struct Want {
     int mode;
-    bool wide, split, tl;
+    bool any;   // quads at any float address (Geometry::any)
+    bool wrap, split, tl;
 };
 
-template <int VEC, int WAVES, int U, bool WIDE, bool SPLIT>
+template <int VEC, bool ANY, int WAVES, int U, bool WRAP, bool SPLIT>
 LaunchFn pick_mode(const Want &w) {
     if (w.tl) {
-        if constexpr (VEC == 4) return &launch_tl<VEC, WAVES, U, WIDE, SPLIT>;
+        if constexpr (VEC == 4 && !ANY) return &launch_tl<VEC, WAVES, U, WRAP, SPLIT>;
         return nullptr;
     }
     switch (w.mode) {
-        case kLisi: return &launch_impl<VEC, WAVES, U, kLisi, WIDE, SPLIT>;
-        case kAug: return &launch_impl<VEC, WAVES, U, kAug, WIDE, SPLIT>;
-        default: return &launch_impl<VEC, WAVES, U, kBoth, WIDE, SPLIT>;
+        case kLisi: return &launch_impl<VEC, ANY, WAVES, U, kLisi, WRAP, SPLIT>;
+        case kAug: return &launch_impl<VEC, ANY, WAVES, U, kAug, WRAP, SPLIT>;
+        default: return &launch_impl<VEC, ANY, WAVES, U, kBoth, WRAP, SPLIT>;
     }
 }
 
-template <int VEC, int WAVES, int U>
+template <int VEC, bool ANY, int WAVES, int U>
 LaunchFn pick_shape(const Want &w) {
-    if (w.wide) {
-        return w.split ? pick_mode<VEC, WAVES, U, true, true>(w)
-                       : pick_mode<VEC, WAVES, U, true, false>(w);
+    if constexpr (VEC == 2) {   // 2 x 2 tiles only: one column
+        if (w.wrap) return nullptr;
+    } else if (w.wrap) {
+        return w.split ? pick_mode<VEC, ANY, WAVES, U, true, true>(w)
+                       : pick_mode<VEC, ANY, WAVES, U, true, false>(w);
     }
-    return w.split ? pick_mode<VEC, WAVES, U, false, true>(w)
-                   : pick_mode<VEC, WAVES, U, false, false>(w);
+    return w.split ? pick_mode<VEC, ANY, WAVES, U, false, true>(w)
+                   : pick_mode<VEC, ANY, WAVES, U, false, false>(w);
 }
 
-template <int VEC, int WAVES>
+template <int VEC, bool ANY, int WAVES>
 LaunchFn pick_unroll(int unroll, const Want &w) {
     switch (unroll) {
-        case 4: return pick_shape<VEC, WAVES, 4>(w);
-        case 8: return pick_shape<VEC, WAVES, 8>(w);
+        case 4: return pick_shape<VEC, ANY, WAVES, 4>(w);
+        case 8: return pick_shape<VEC, ANY, WAVES, 8>(w);
         default: return nullptr;
     }
 }
 
 // The instantiated launch shapes: waves 1/2/4/8 with unroll 4/8 and waves 16
-// with unroll 4 for vec 4, and waves 1/4 with unroll 4 for the narrow vec 2
-// and vec 1 paths; each with and without a row split across workgroups.
+// with unroll 4 for vec 4, and waves 1/4 with unroll 4 for vec 2 and vec 1;
+// each with and without a row split across workgroups.  vec 2 and vec 1 run
+// the any-address quad kernel for NT >= 4 and the narrow loads below that.
 // Timeline launches exist for the vec 4 shapes, fused mode.
 LaunchFn pick(const iqa_launch_cfg &c, const Want &w) {
     if (c.vec == 4) {
         switch (c.waves) {
-            case 1: return pick_unroll<4, 1>(c.unroll, w);
-            case 2: return pick_unroll<4, 2>(c.unroll, w);
-            case 4: return pick_unroll<4, 4>(c.unroll, w);
-            case 8: return pick_unroll<4, 8>(c.unroll, w);
-            case 16: return c.unroll == 4 ? pick_shape<4, 16, 4>(w) : nullptr;
+            case 1: return pick_unroll<4, false, 1>(c.unroll, w);
+            case 2: return pick_unroll<4, false, 2>(c.unroll, w);
+            case 4: return pick_unroll<4, false, 4>(c.unroll, w);
+            case 8: return pick_unroll<4, false, 8>(c.unroll, w);
+            case 16: return c.unroll == 4 ? pick_shape<4, false, 16, 4>(w) : nullptr;
             default: return nullptr;
         }
     }
     if (w.tl || c.unroll != 4 || !(c.waves == 1 || c.waves == 4)) return nullptr;
-    if (c.vec == 2) return c.waves == 1 ? pick_shape<2, 1, 4>(w) : pick_shape<2, 4, 4>(w);
-    if (c.vec == 1) return c.waves == 1 ? pick_shape<1, 1, 4>(w) : pick_shape<1, 4, 4>(w);
+    if (w.any) return c.waves == 1 ? pick_shape<4, true, 1, 4>(w) : pick_shape<4, true, 4, 4>(w);
+    if (c.vec == 2) return c.waves == 1 ? pick_shape<2, false, 1, 4>(w) : pick_shape<2, false, 4, 4>(w);
+    if (c.vec == 1) return c.waves == 1 ? pick_shape<1, false, 1, 4>(w) : pick_shape<1, false, 4, 4>(w);
     return nullptr;
 }
 
@@ -1108,7 +1163,9 @@ iqa_status check_shape(int64_t N, int64_t NT) {
 
 struct Geometry {
     int64_t ns, ht, ngx, groups, grid;
-    int lpt, cpl;
+    int log_grp;
+    int cols;
+    bool any, wrap;
 };
 
 iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g) {
@@ -1116,23 +1173,44 @@ iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g)
     if (!is_pow2(c.seg) || !is_pow2(c.rp) || (int64_t)c.seg * c.rp > kWave) return IQA_ERR_CONFIG;
     if (!is_pow2(c.waves) || c.waves > 16) return IQA_ERR_CONFIG;
     if (c.ksplit < 1 || NT % ((int64_t)c.waves * c.ksplit) != 0) return IQA_ERR_CONFIG;
-    if (pick(c, Want{kBoth, false, false, false}) == nullptr) return IQA_ERR_CONFIG;
+    // vec 2 and vec 1 stand for images whose rows or tiles 16-byte loads do
+    // not fit.  From NT = 4 on they run quads at any float address: the same
+    // lanes per tile, one 16-byte load at 4-byte alignment in place of four
+    // 4-byte or two 8-byte ones.
+    g.any = c.vec < 4 && NT >= 4;
+    if (pick(c, Want{kBoth, g.any, false, false, false}) == nullptr) return IQA_ERR_CONFIG;
     g.ns = N / NT;
-    g.ht = kWave / ((int64_t)c.seg * c.rp);
+    g.log_grp = ilog2((int64_t)c.seg * c.rp);
+    g.ht = kWave >> g.log_grp;
     g.ngx = (g.ns + g.ht - 1) / g.ht;
     g.groups = g.ns * g.ngx;
     g.grid = g.groups * c.ksplit;
-    g.lpt = (int)(NT / c.vec);
-    g.cpl = (int)((g.lpt + c.seg - 1) / c.seg);
+    g.cols = (int)(g.any ? (NT + 3) / 4 : NT / c.vec);
+    g.wrap = g.cols > 1 << g.log_grp;
     if (g.grid > (int64_t)INT_MAX) return IQA_ERR_CONFIG;
     return IQA_OK;
 }
 
 // Built-in launch shape for (N, NT), for shapes the autotuner has not
-// measured: widest aligned vector, one segment per tile row (up to a full
-// wave), two row phases per wave, enough waves per workgroup that each lane
-// reduces ~16 rows, and row splits across workgroups while the launch has
-// fewer than ~4 waves per CU.  (The measured shapes cluster around this.)
+// measured: the widest vector the images' alignment and NT allow (vec 2 and
+// vec 1 run any-address quads, one wave per workgroup unless 4 divides NT),
+// four waves per workgroup, and batches of four rows.  Two rules follow.
+//
+// Lanes per tile.  A wave covers as many adjacent tiles as fit, one row of
+// quads each, unless that leaves too few workgroups or too many items per
+// lane; then it takes fewer tiles and more rows of each.  The lines, in us:
+//   vec 4: 256 workgroups (1000^2/100: 100 workgroups 5.7, 50 6.1; 3000^2/100:
+//          450 workgroups 13.9, 900 14.5), and 8 items where a row is at most
+//          16 quads (3840^2/40: 5 items 21.1, 10 items 21.9).
+//          At 32 lanes a row, two rows if a tile row is whole 128-byte lines
+//          (3840^2/96: 21.0, one row of two tiles 23.3), else one row of two
+//          tiles, which share the line between them (3840^2/120: 20.6, two
+//          rows above 22);
+//   else:  1200 waves (2000^2/50: 1600 waves 8.0, 800 9.0; 8190^2/63: 4290
+//          waves 90.6, 8450 93.1), and 16 items where a row is at most 8
+//          quads (2025^2/25: 11 items 7.9, 22 items 9.1).
+//
+// Row splits across workgroups while the launch has fewer than ~4 waves per CU.
 constexpr int64_t kTargetWaves = 1024;
 
 iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y) {
@@ -1140,25 +1218,34 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     c.vec = 1;
     if (NT % 2 == 0 && aligned(x, 8) && aligned(y, 8)) c.vec = 2;
     if (NT % 4 == 0 && aligned(x, 16) && aligned(y, 16)) c.vec = 4;
-    const int64_t lpt = NT / c.vec;
-    c.seg = (int)std::min<int64_t>(kWave, next_pow2(lpt));
-    const int64_t tpw = kWave / c.seg;     // segments per wave
+    c.unroll = 4;
+    c.waves = NT % 4 == 0 ? 4 : 1;
+    c.ksplit = 1;
+    const bool any = c.vec < 4 && NT >= 4;
+    const int64_t cols = any ? (NT + 3) / 4 : NT / c.vec;
+    const int64_t row_lanes = std::min<int64_t>(kWave, next_pow2(cols));
     const int64_t ns = N / NT;
-    const int64_t rp = std::min<int64_t>(2, tpw);
-    c.rp = (int)rp;
-    const int64_t ht = tpw / rp;
-    const int64_t groups = ns * ((ns + ht - 1) / ht);
-    int64_t kw = 1;
-    const int64_t kw_max = c.vec == 4 ? 16 : 4;
-    while (kw < kw_max && NT % (kw * 2) == 0 && NT / (rp * kw * 2) >= 16) kw *= 2;
-    if (c.vec != 4 && kw > 1) kw = (NT % 4 == 0) ? 4 : 1;
-    int64_t ks = 1;
-    while (groups * kw * ks < kTargetWaves && NT % (kw * ks * 2) == 0 &&
-           NT / (rp * kw * ks * 2) >= 4)
-        ks *= 2;
-    c.waves = (int)kw;
-    c.unroll = (c.vec == 4 && kw <= 8) ? 8 : 4;
-    c.ksplit = (int)ks;
+    const int64_t rows = NT / c.waves;     // per wave
+    int64_t lanes = row_lanes;
+    auto workgroups = [&] { return ns * ((ns * lanes + kWave - 1) / kWave); };
+    auto items = [&](int64_t r) {
+        return (r * (cols > kWave ? cols : row_lanes) + lanes - 1) / lanes;
+    };
+    while (lanes < kWave) {
+        const bool few = c.vec == 4 ? workgroups() < 256 : workgroups() * c.waves < 1200;
+        const bool long_lane = row_lanes <= (c.vec == 4 ? 16 : 8) &&
+                               items(rows) > (c.vec == 4 ? 8 : 16);
+        const bool whole_lines = c.vec == 4 && row_lanes == 32 && NT % 32 == 0;
+        if (!few && !long_lane && !whole_lines) break;
+        lanes *= 2;
+    }
+    c.seg = (int)std::min<int64_t>(lanes, next_pow2(NT / c.vec));
+    c.rp = (int)(lanes / c.seg);
+    const int64_t groups = workgroups();
+    const int64_t rp = std::max<int64_t>(1, lanes / row_lanes);
+    while (groups * c.waves * c.ksplit < kTargetWaves && NT % (c.waves * c.ksplit * 2) == 0 &&
+           NT / (rp * c.waves * c.ksplit * 2) >= 4)
+        c.ksplit *= 2;
     return c;
 }
 
@@ -1360,32 +1447,37 @@ iqa_status scratch_for_current_device(float **out) {
     return IQA_OK;
 }
 
-void fill_args(KArgs &a, const float *x, const float *y, int64_t N, int64_t NT, float D,
+void fill_pair(PairArgs &a, const float *x, const float *y, int64_t N, int64_t NT, float D,
                float C1, float C2, float C, float *lisi, float *aug, float *sums,
                const iqa_launch_cfg &c, const Geometry &g) {
     a.x = x;
     a.y = y;
-    a.N = (int32_t)N;
-    a.smode = kSplitNone;
-    a.NT = (int32_t)NT;
-    a.ns = (int32_t)g.ns;
-    a.ngx = (int32_t)g.ngx;
-    a.log_seg = ilog2(c.seg);
-    a.log_grp = ilog2((int64_t)c.seg * c.rp);
-    a.ht = (int32_t)g.ht;
-    a.ks = c.ksplit;
-    a.rows_wave = (int32_t)(NT / ((int64_t)c.waves * c.ksplit));
-    a.lpt = g.lpt;
-    a.cpl = g.cpl;
-    a.ngx_m = div_magic(g.ngx);
-    a.ks_m = div_magic(c.ksplit);
+    a.lisi = lisi;
+    a.aug = aug;
+    a.sums = sums;
     a.D = D;
     a.C1 = C1;
     a.C2 = C2;
     a.C = C;
-    a.lisi = lisi;
-    a.aug = aug;
-    a.sums = sums;
+    a.N = (int32_t)N;
+    a.NT = (int32_t)NT;
+    a.ns = (int32_t)g.ns;
+    a.ngx = (int32_t)g.ngx;
+    a.ngx_m = div_magic(g.ngx);
+    a.log_grp = g.log_grp;
+    a.rows_wave = (int32_t)(NT / ((int64_t)c.waves * c.ksplit));
+    const int64_t lanes = int64_t(1) << g.log_grp;
+    const int64_t pitch = g.wrap ? g.cols : next_pow2(g.cols);
+    a.cols = g.cols;
+    a.pitch = (int32_t)pitch;
+    a.pitch_m = (uint32_t)(((int64_t(1) << 31) + pitch - 1) / pitch);
+    const int64_t places = a.rows_wave * pitch;
+    a.items = (places + lanes - 1) / lanes;
+    const int64_t shift = a.items * lanes - places;
+    a.lead_rows = (int32_t)((shift + pitch - 1) / pitch);
+    a.lead = (int32_t)(a.lead_rows * pitch - shift);
+    const int64_t quad_bytes = 4 * (g.any ? 4 : c.vec);
+    a.step = (int32_t)(g.wrap ? lanes * quad_bytes : lanes / pitch * N * 4);
 }
 
 hipError_t launch_combine(const KArgs &a, int mode, const Geometry &g, hipStream_t s) {
@@ -1414,7 +1506,7 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
     }
     int mode = ((lisi || sums) ? kLisi : 0) | ((aug || sums) ? kAug : 0);
     if (mode == 0) mode = kBoth;
-    LaunchFn fn = pick(c, Want{mode, g.cpl > 1, c.ksplit > 1, tl != nullptr});
+    LaunchFn fn = pick(c, Want{mode, g.any, g.wrap, c.ksplit > 1, tl != nullptr});
     if (!fn) return IQA_ERR_CONFIG;
     hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -1443,8 +1535,10 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
     }
     if (ws == Ws::kPrepare) return IQA_OK;
 
-    fill_args(a, x, y, N, NT, D, C1, C2, C, lisi, aug, sums, c, g);
+    fill_pair(a, x, y, N, NT, D, C1, C2, C, lisi, aug, sums, c, g);
     a.smode = split_mode(g, c);
+    a.ks = c.ksplit;
+    a.ks_m = div_magic(c.ksplit);
     hipError_t e = fn(a, tl, (unsigned)g.grid, s);
     if (e == hipSuccess && a.smode == kSplitCombine) e = launch_combine(a, mode, g, s);
     return hip_status(e);
@@ -1656,7 +1750,7 @@ iqa_status iqa::describe_pairs(const iqa_pair *pairs, int64_t count, void *descs
         std::memset(&d, 0, sizeof(d));
         // Outputs a pair does not ask for stay NULL; the batch always computes
         // all four sums, so lisi and auglisi get the constants they need.
-        fill_args(d.a, p.x, p.y, p.N, p.NT, p.lisi || p.sums ? p.D : 1.f,
+        fill_pair(d.a, p.x, p.y, p.N, p.NT, p.lisi || p.sums ? p.D : 1.f,
                   p.lisi || p.sums ? p.C1 : 1.f, p.lisi || p.sums ? p.C2 : 1.f,
                   p.auglisi || p.sums ? p.C : 1.f, p.lisi, p.auglisi, p.sums, c, g);
         d.unit_begin = units;
