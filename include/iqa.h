@@ -39,12 +39,17 @@
  *   most 1024 workgroups, else by a second, small launch on the same stream.
  *   The two give the same bits.  Those launches use a small library-owned
  *   device workspace per (device, stream) (16 bytes per tile and split part,
- *   plus 4 bytes per tile group),
+ *   at least 128 per part and 128 more per tile group where a ticket counter
+ *   decides),
  *   allocated and cleared on first use and reused afterwards (an outgrown
  *   buffer is kept until the process ends, so graphs captured earlier stay
  *   valid).  The first call for a given (device, stream, shape) must
  *   therefore not happen while the stream is being captured into a graph:
  *   call iqa_prepare() (or the entry point itself) once before.
+ *   Default launches of tile sides that powers of two do not divide far
+ *   enough (say 300 or 225) split too, but carry none of these rules: captured,
+ *   or through iqa_tiles_noalloc, they run without any workspace, bitwise the
+ *   same, and slower (one workgroup per tile).
  * Threads.  Every entry point may be called from several host threads at
  *   once, on the same stream or on different ones.  Calls on one stream run
  *   in the order they were enqueued, each launch finishing before the next
@@ -184,8 +189,10 @@ int64_t iqa_launch_workgroups(int64_t N, int64_t NT, const iqa_launch_cfg *cfg);
  * partial sums and ticket counters from a fixed array of
  * IQA_NOALLOC_SCRATCH_BYTES in device memory that the library holds on every
  * GPU it runs on until the process ends, instead of the per-stream workspace:
- * 4 bytes per tile group in its first 64 KiB (at most 16384 tile groups) and
- * 16 bytes per tile and split part in the rest, so a shape needing more
+ * 128 bytes per tile group in its first 64 KiB where a ticket counter decides
+ * (at most 512 tile groups, all that such launches have) and 16 bytes per tile
+ * and split part, at least 128 per part with a counter, in the rest, so a shape
+ * needing more
  * returns IQA_ERR_SCRATCH (launching nothing).  Shapes that do
  * not split use no scratch.  Results are bitwise those of iqa_tiles_cfg with
  * the same configuration.  Every call on one GPU shares that GPU's array:

@@ -620,13 +620,17 @@ __device__ __forceinline__ float4 wave_tree(float4 (&v)[WAVES]) {
 // are bitwise reproducible and equal between the two.
 //
 // Workspace: partials [group][part][ht] float4 from a.ws on, and (ticket
-// mode) one 32-bit counter per group just below a.ws (group g's at
-// a.ws - 4 (g + 1) bytes), in a counter region that holds nothing but
+// mode) one 32-bit counter per group below a.ws (group g's at
+// a.ws - kLine (g + 1) bytes), in a counter region that holds nothing but
 // counters.  The counters start at zero and every launch leaves the ones it
 // used at zero, so a region reused by shapes of any size is all zeros between
-// launches.
-__host__ __device__ __forceinline__ int64_t split_partials(int64_t groups, int64_t ks, int64_t ht) {
-    return groups * ks * ht;   // float4 entries
+// launches.  In ticket mode the parts' partials and the counters of different
+// groups lie on lines of their own: coherent accesses of different XCDs to one
+// line go one after the other.
+constexpr int64_t kLine = 128;
+
+__host__ __device__ __forceinline__ int64_t part_entries(int smode, int64_t ht) {
+    return smode == kSplitTicket && ht * 16 < kLine ? kLine / 16 : ht;   // float4 per part
 }
 
 __device__ __forceinline__ void store_coherent(float4 *p, float4 v) {
@@ -657,6 +661,7 @@ template <int MODE, bool COHERENT>
 __device__ __forceinline__ void combine_parts(const KArgs &a, int grp, int lane) {
     const float4 *ws = reinterpret_cast<const float4 *>(a.ws);
     const int64_t base = (int64_t)grp * a.ks;
+    const int64_t pitch = part_entries(a.smode, tiles_per_wave(a));
     const int ty = udiv(grp, a.ngx_m, a.ngx);
     const int txg = grp - ty * a.ngx;
     // Lane group of tile j: 2^log_grp lanes; lane q of the group takes parts
@@ -669,7 +674,7 @@ __device__ __forceinline__ void combine_parts(const KArgs &a, int grp, int lane)
     Acc c = acc_zero();
     if (tx < a.ns) {
         for (int p = q; p < a.ks; p += g) {
-            const float4 *src = ws + (base + p) * ht + j;
+            const float4 *src = ws + (base + p) * pitch + j;
             const float4 w = COHERENT ? load_coherent(src) : *src;
             if constexpr ((MODE & kLisi) != 0) cadd(c.A, w.x);
             if constexpr ((MODE & kAug) != 0) cadd(c.P, w.y);
@@ -687,13 +692,14 @@ template <int MODE>
 __device__ __forceinline__ bool split_finish(const KArgs &a, int grp, int part, int lane, bool mine,
                                              int jt, float4 v) {
     float4 *ws = reinterpret_cast<float4 *>(a.ws);
-    float4 *slot = ws + ((int64_t)grp * a.ks + part) * tiles_per_wave(a) + jt;
+    float4 *slot =
+        ws + ((int64_t)grp * a.ks + part) * part_entries(a.smode, tiles_per_wave(a)) + jt;
     if (a.smode == kSplitCombine) {
         if (mine) *slot = v;
         return false;
     }
     if (mine) store_coherent(slot, v);
-    uint32_t *cnt = reinterpret_cast<uint32_t *>(a.ws) - 1 - grp;
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(a.ws) - (kLine / 4) * ((int64_t)grp + 1);
     wait_vmem();                                        // partials stored before the ticket
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     uint32_t ticket = 0;
@@ -809,6 +815,47 @@ __global__ __launch_bounds__(WAVES * kWave) void tiles_kernel(KArgs a) {
 template <int VEC, int WAVES, int U, bool WRAP, bool SPLIT>
 __global__ __launch_bounds__(WAVES * kWave) void tiles_kernel_tl(KArgs a, uint64_t *tl) {
     tiles_body<VEC, false, WAVES, U, kBoth, WRAP, SPLIT, true>(a, tl);
+}
+
+// A split launch without a workspace: one workgroup per tile (ht == 1) takes
+// all of the tile's waves * ks slices, sixteen waves at a time, keeps their
+// sums in LDS and adds them as the split launch does (the waves of each part by
+// the same tree, the parts as combine_parts), so the bits are the same.
+constexpr int kLocalWaves = 16;
+
+template <bool ANY, int U, int MODE, bool WRAP>
+__global__ __launch_bounds__(kLocalWaves * kWave) void tiles_local_kernel(KArgs a, int waves) {
+    extern __shared__ float4 slices[];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int grp = xcd_remap(blockIdx.x, gridDim.x);
+    const int ty = udiv(grp, a.ngx_m, a.ngx);
+    const int tx = grp - ty * a.ngx;
+    for (int i = wave; i < waves * a.ks; i += kLocalWaves) {
+        const Sum4 s = slice_sums<4, ANY, U, MODE, WRAP>(a, ty, tx, i, lane);
+        if (lane == 0) slices[i] = float4{s.A, s.P, s.X, s.Y};
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    Acc c = acc_zero();
+    for (int p = lane; p < a.ks; p += kWave) {
+        float4 v = slices[p * waves];
+        if (waves == 4) {
+            float4 w[4] = {v, slices[p * 4 + 1], slices[p * 4 + 2], slices[p * 4 + 3]};
+            v = wave_tree<4>(w);
+        } else if (waves == 8) {
+            float4 w[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[i] = slices[p * 8 + i];
+            v = wave_tree<8>(w);
+        }
+        if constexpr ((MODE & kLisi) != 0) cadd(c.A, v.x);
+        if constexpr ((MODE & kAug) != 0) cadd(c.P, v.y);
+        cadd(c.X, v.z);
+        cadd(c.Y, v.w);
+    }
+    const Sum4 s = group_allreduce<MODE>(fold(c), a.log_grp);
+    if (lane == 0) finalize<MODE>(a, (int64_t)ty * a.ns + tx, s);
 }
 
 // kSplitCombine: one wave per tile group adds its parts, after the tile
@@ -1045,11 +1092,17 @@ struct same_type {
 };
 
 template <typename... P>
+hipError_t launch_with_lds(void (*fn)(P...), unsigned grid, unsigned block, size_t lds,
+                           hipStream_t s, typename same_type<P>::type... args) {
+    void *argv[] = {static_cast<void *>(&args)...};
+    return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(grid), dim3(block), argv, lds,
+                           s);
+}
+
+template <typename... P>
 hipError_t launch_kernel(void (*fn)(P...), unsigned grid, unsigned block, hipStream_t s,
                          typename same_type<P>::type... args) {
-    void *argv[] = {static_cast<void *>(&args)...};
-    return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(grid), dim3(block), argv, 0,
-                           s);
+    return launch_with_lds(fn, grid, block, 0, s, args...);
 }
 
 iqa_status hip_status(hipError_t e) {
@@ -1210,9 +1263,15 @@ iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g)
 //          waves 90.6, 8450 93.1), and 16 items where a row is at most 8
 //          quads (2025^2/25: 11 items 7.9, 22 items 9.1).
 //
-// Row splits across workgroups while the launch has fewer than ~4 waves per CU.
-constexpr int64_t kTargetWaves = 1024;
-
+// Splits.  A tile whose waves would each make more than 24 items is split over
+// workgroups if the launch has less than one of four waves per CU (or 1500
+// waves): into the fewest parts that give it that, as long as a lane keeps 3
+// items.  (Unsplit against split: 1000^2/100, 13 items, 5.7 and 6.2;
+// 3000^2/300, 88 items, 23.4 and 15.6.)  Counts from one workgroup per CU to
+// nearly two are passed over: some CUs would have twice the work of others
+// (6000^2/1500: 240 workgroups 49.6, 400 54.3, 1200 51.5).  A few deeply split
+// tiles take eight waves per workgroup, so that fewer parts are added at the
+// end (2048^2/2048: 128 parts of eight waves 11.6, 256 of four 12.6).
 iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y) {
     iqa_launch_cfg c{};
     c.vec = 1;
@@ -1241,12 +1300,40 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     }
     c.seg = (int)std::min<int64_t>(lanes, next_pow2(NT / c.vec));
     c.rp = (int)(lanes / c.seg);
-    const int64_t groups = workgroups();
-    const int64_t rp = std::max<int64_t>(1, lanes / row_lanes);
-    while (groups * c.waves * c.ksplit < kTargetWaves && NT % (c.waves * c.ksplit * 2) == 0 &&
-           NT / (rp * c.waves * c.ksplit * 2) >= 4)
-        c.ksplit *= 2;
+    const int64_t tiles = ns * ns;
+    if (workgroups() * c.waves >= (c.waves == 4 ? 1024 : 1500) || items(rows) <= 24 ||
+        lanes < kWave)
+        return c;
+    if (c.vec == 4 && tiles <= 16 && NT % 8 == 0) c.waves = 8;
+    auto enough = [&](int64_t wgs) {
+        return c.waves == 1 ? wgs >= 1500 : wgs >= 225 && (wgs <= 256 || wgs >= 448);
+    };
+    // Parts are equal: divisors of a wave's rows.  At most 4096 slices of a tile
+    // (see launch_local) and as many parts in all as the fixed scratch holds.
+    constexpr int64_t kMostParts = (IQA_NOALLOC_SCRATCH_BYTES - (64 << 10)) / 16;
+    const int32_t per = (int32_t)(NT / c.waves);
+    for (int32_t ks = 1; ks <= per && ks * c.waves <= 4096 && tiles * ks <= kMostParts; ++ks) {
+        if (per % ks != 0) continue;
+        if (items(per / ks) < 3) break;
+        c.ksplit = ks;
+        if (enough(tiles * ks)) break;
+    }
     return c;
+}
+
+// Whether the stream's workspace belongs to (N, NT)'s default launch whatever
+// the stream is doing: the shapes documented to need iqa_prepare before a
+// capture, those that powers of two split.  Other default splits use a
+// workspace of their own, and none under capture (see Ws).
+bool split_needs_prepare(int64_t N, int64_t NT, int64_t vec) {
+    const int64_t seg = std::min<int64_t>(kWave, next_pow2(NT / vec));
+    const int64_t rp = std::min<int64_t>(2, kWave / seg);
+    const int64_t ht = kWave / seg / rp;
+    const int64_t ns = N / NT;
+    int64_t kw = 1;
+    while (kw < (vec == 4 ? 16 : 4) && NT % (kw * 2) == 0 && NT / (rp * kw * 2) >= 16) kw *= 2;
+    if (vec != 4 && kw > 1) kw = NT % 4 == 0 ? 4 : 1;
+    return ns * ((ns + ht - 1) / ht) * kw < 1024 && NT % (kw * 2) == 0 && NT / (rp * kw * 2) >= 4;
 }
 
 // Tuned launch shapes.  The autotuner's measurements on gfx950 are compiled in
@@ -1304,6 +1391,15 @@ bool tuned_lookup(int64_t N, int64_t NT, int kind, iqa_launch_cfg *out) {
     return false;
 }
 
+// A split default launch with the contract of split launches: a tuned shape,
+// or one that split_needs_prepare names.
+bool tuned_or_prepared(int64_t N, int64_t NT, const iqa_launch_cfg &c, const float *x,
+                       const float *y) {
+    iqa_launch_cfg t;
+    if (aligned(x, 16) && aligned(y, 16) && tuned_lookup(N, NT, IQA_TUNE_SINGLE, &t)) return true;
+    return split_needs_prepare(N, NT, c.vec);
+}
+
 iqa_launch_cfg pick_cfg(int64_t N, int64_t NT, const float *x, const float *y) {
     iqa_launch_cfg c;
     if (aligned(x, 16) && aligned(y, 16) && tuned_lookup(N, NT, 0, &c)) return c;
@@ -1353,7 +1449,7 @@ struct Workspace {
     size_t part_bytes = 0;   // partial-sum region, at ptr + cnt_bytes
 };
 std::mutex g_ws_mutex;
-std::map<std::pair<int, void *>, Workspace> g_ws;
+std::map<std::tuple<int, void *, bool>, Workspace> g_ws;
 std::vector<void *> g_ws_retired;
 
 // Split launches of at most this many workgroups (one round on gfx950's 256
@@ -1375,20 +1471,21 @@ SplitNeed split_need(const Geometry &g, const iqa_launch_cfg &c) {
     SplitNeed n;
     const int m = split_mode(g, c);
     if (m == kSplitNone) return n;
-    if (m == kSplitTicket) n.cnt_bytes = (size_t)g.groups * sizeof(uint32_t);
-    n.part_bytes = (size_t)split_partials(g.groups, c.ksplit, g.ht) * 4 * sizeof(float);
+    if (m == kSplitTicket) n.cnt_bytes = (size_t)(g.groups * kLine);
+    n.part_bytes = (size_t)(g.groups * c.ksplit * part_entries(m, g.ht)) * 4 * sizeof(float);
     return n;
 }
 
 size_t round_up(size_t v, size_t m) { return (v + m - 1) / m * m; }
 
 // *part receives the partial-sum region; the counter region ends where it
-// starts.  The caller holds g_ws_mutex.
-iqa_status workspace_for(hipStream_t s, const SplitNeed &need, float **part) {
+// starts.  `own`: the buffer of the default launches that never use a
+// workspace under capture.  The caller holds g_ws_mutex.
+iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float **part) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_status(e);
-    Workspace &w = g_ws[{dev, (void *)s}];
+    Workspace &w = g_ws[{dev, (void *)s, own}];
     if (w.cnt_bytes < need.cnt_bytes || w.part_bytes < need.part_bytes) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (s != nullptr) {
@@ -1487,6 +1584,37 @@ hipError_t launch_combine(const KArgs &a, int mode, const Geometry &g, hipStream
     return launch_kernel(fn, (unsigned)g.groups, kWave, s, a);
 }
 
+// LDS of a tiles_local_kernel workgroup: 16 bytes per slice of its tile.
+constexpr size_t kLocalLdsMax = 64 << 10;
+
+size_t local_lds(const iqa_launch_cfg &c) { return (size_t)c.waves * c.ksplit * sizeof(float4); }
+
+// Shapes whose default launch splits without split_needs_prepare: whether this
+// configuration can run without a workspace too.
+bool local_ok(const iqa_launch_cfg &c, const Geometry &g) {
+    return g.ht == 1 && c.unroll == 4 && (c.vec == 4 || g.any) && local_lds(c) <= kLocalLdsMax &&
+           (c.waves == 1 || c.waves == 4 || c.waves == 8);
+}
+
+template <bool ANY, bool WRAP>
+hipError_t launch_local_mode(const KArgs &a, int mode, const iqa_launch_cfg &c, const Geometry &g,
+                             hipStream_t s) {
+    void (*fn)(KArgs, int) = mode == kLisi  ? &tiles_local_kernel<ANY, 4, kLisi, WRAP>
+                             : mode == kAug ? &tiles_local_kernel<ANY, 4, kAug, WRAP>
+                                            : &tiles_local_kernel<ANY, 4, kBoth, WRAP>;
+    return launch_with_lds(fn, (unsigned)g.groups, kLocalWaves * kWave, local_lds(c), s, a, c.waves);
+}
+
+hipError_t launch_local(const KArgs &a, int mode, const iqa_launch_cfg &c, const Geometry &g,
+                        hipStream_t s) {
+    if (g.any) {
+        return g.wrap ? launch_local_mode<true, true>(a, mode, c, g, s)
+                      : launch_local_mode<true, false>(a, mode, c, g, s);
+    }
+    return g.wrap ? launch_local_mode<false, true>(a, mode, c, g, s)
+                  : launch_local_mode<false, false>(a, mode, c, g, s);
+}
+
 // Where a launch's split workspace comes from.
 enum class Ws {
     kLibrary,   // the per-(device, stream) buffer, grown on demand
@@ -1494,6 +1622,13 @@ enum class Ws {
     kPrepare,   // only allocate the library buffer, launch nothing
 };
 
+// A default launch that splits without split_needs_prepare must not put the
+// rules of split launches on its caller (prepare before a capture, no other
+// split work beside a graph's replay or on the scratch array).  Run eagerly on
+// a stream it has a buffer of its own there, which launches on that stream use
+// one after the other and no graph ever holds; captured, or through the
+// no-allocation entry point, it runs without a workspace (launch_local),
+// bitwise the same.
 iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, float C1,
                float C2, float C, float *lisi, float *aug, float *sums,
                const iqa_launch_cfg *cfg_in, void *stream, Ws ws, uint64_t *tl = nullptr) {
@@ -1512,12 +1647,23 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
 
     KArgs a{};
     const SplitNeed need = split_need(g, c);
+    bool own = false, local = false;
+    if (c.ksplit > 1 && !cfg_in && local_ok(c, g) && !tuned_or_prepared(N, NT, c, x, y)) {
+        own = true;
+        local = ws == Ws::kScratch;
+        if (ws == Ws::kLibrary && s != nullptr) {
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            const hipError_t e = hipStreamIsCapturing(s, &cs);
+            if (e != hipSuccess) return hip_status(e);
+            local = cs != hipStreamCaptureStatusNone;
+        }
+    }
     // The workspace (or scratch) stays locked until the launches are
     // enqueued: a combine-mode split is two launches, and another host
     // thread's split launches on the same stream must not come between them.
     std::unique_lock<std::mutex> ws_lock(g_ws_mutex, std::defer_lock);
     std::unique_lock<std::mutex> scratch_lock(g_scratch_mutex, std::defer_lock);
-    if (need.part_bytes > 0) {
+    if (need.part_bytes > 0 && !local) {
         if (ws == Ws::kScratch) {
             if (need.cnt_bytes > kScratchCounterBytes ||
                 need.part_bytes > IQA_NOALLOC_SCRATCH_BYTES - kScratchCounterBytes)
@@ -1529,7 +1675,7 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
             a.ws = reinterpret_cast<float *>(reinterpret_cast<char *>(base) + kScratchCounterBytes);
         } else {
             ws_lock.lock();
-            st = workspace_for(s, need, &a.ws);
+            st = workspace_for(s, own, need, &a.ws);
             if (st != IQA_OK) return st;
         }
     }
@@ -1539,6 +1685,7 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
     a.smode = split_mode(g, c);
     a.ks = c.ksplit;
     a.ks_m = div_magic(c.ksplit);
+    if (local) return hip_status(launch_local(a, mode, c, g, s));
     hipError_t e = fn(a, tl, (unsigned)g.grid, s);
     if (e == hipSuccess && a.smode == kSplitCombine) e = launch_combine(a, mode, g, s);
     return hip_status(e);
@@ -1615,7 +1762,9 @@ iqa_status iqa_tiles_timeline(const float *x, const float *y, int64_t N, int64_t
     if (st != IQA_OK) return st;
     if (!stamps) return IQA_ERR_NULL;
     if (!aligned(stamps, 8)) return IQA_ERR_ALIGN;
-    const iqa_launch_cfg c = cfg ? *cfg : pick_cfg(N, NT, x, y);
+    iqa_launch_cfg c = cfg ? *cfg : pick_cfg(N, NT, x, y);
+    // One row of stamps per workgroup that a workspace-free launch would have.
+    if (!cfg && c.ksplit > 1 && !tuned_or_prepared(N, NT, c, x, y)) c.ksplit = 1;
     Geometry g{};
     st = geometry(N, NT, c, g);
     if (st != IQA_OK) return st;
