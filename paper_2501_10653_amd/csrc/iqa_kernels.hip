@@ -626,7 +626,10 @@ __device__ __forceinline__ float4 wave_tree(float4 (&v)[WAVES]) {
 // used at zero, so a region reused by shapes of any size is all zeros between
 // launches.  In ticket mode the parts' partials and the counters of different
 // groups lie on lines of their own: coherent accesses of different XCDs to one
-// line go one after the other.
+// line go one after the other.  (With 16-byte partials and 4-byte counters
+// side by side a ticket launch paid about 10 ns per workgroup: 1000^2/250 in 50
+// parts 14.0 us against 6.1, 2048^2/512 in 16 parts of sixteen waves 10.9
+// against 9.1.)
 constexpr int64_t kLine = 128;
 
 __host__ __device__ __forceinline__ int64_t part_entries(int smode, int64_t ht) {
