@@ -151,7 +151,8 @@ typedef struct iqa_launch_cfg {
     int32_t vec;     /* floats of alignment the loads rely on: 4, 2 or 1; NT % vec == 0.
                         Tiles of NT >= 4 are read 4 floats per lane load either way,
                         vec 2 and vec 1 at any float address */
-    int32_t waves;   /* waves per workgroup: 1, 2, 4, 8 or 16 (vec 4); 1 or 4 (vec 1, 2) */
+    int32_t waves;   /* waves per workgroup: 1, 2, 4, 8 or 16 (vec 4); 1 or 4 (vec 1, 2:
+                        four run for NT >= 4, on quarters of the rows, uneven if need be) */
     int32_t unroll;  /* rows per load batch: 4 or 8 (vec 4, waves <= 8); 4 otherwise */
     int32_t seg;     /* lanes per tile row segment: power of two, 1..64 */
     int32_t rp;      /* row phases per tile in a wave: power of two, seg*rp <= 64 */

@@ -69,11 +69,11 @@ struct PairArgs {
     int32_t ngx;         // tile groups along x: ceil(ns / ht)
     uint32_t ngx_m;      // division multiplier for ngx (see udiv)
     int32_t log_grp;     // log2(G), lanes per tile in a wave; ht = 64 / G tiles per wave
-    int32_t rows_wave;   // tile rows per wave slice: NT / (waves * ks)
+    int32_t rows_wave;   // tile rows per wave slice: NT / (waves * ks); ANY: per part, NT / ks
     int32_t cols;        // quads (VEC pixels) per tile row: ceil(NT / vec)
     int32_t pitch;       // quad places per tile row that the lanes count with
     uint32_t pitch_m;    // ceil(2^31 / pitch)
-    int32_t lead;        // lead_rows * pitch - shift
+    int32_t lead;        // lead_rows * pitch - shift (these three: not ANY)
     int32_t lead_rows;   // rows above the slice that lane 0 starts counting from
     int32_t step;        // bytes from one of a lane's items to the next, before a wrap
     int64_t items;       // loads per lane and image: ceil(rows_wave * pitch / G)
@@ -447,6 +447,13 @@ __device__ __forceinline__ uint64_t stamp_after(float v) {
 // ANY (VEC 4): images at any float address and any NT >= 4.  A lane loads a
 // quad wherever it lies; the last quad of a tile row is moved back to end with
 // the row, and the pixels it then shares with its neighbour are not counted.
+// NT may be odd, so the slices are quarters of a part's rows, uneven by a row,
+// and their items are counted here.  (One wave per part against four, each with
+// its best lanes per tile, in us: 2025^2/45 9.1 and 8.4, 8190^2/90 92.5 and
+// 85.8, 500^2/50 5.0 and 4.0, 1000^2/250 6.2 and 5.5; 2000^2/50 8.1 both;
+// 2025^2/25 7.6 and 8.3, 3000^2/75 15.4 and 16.1.  Two waves lie between.)
+constexpr int kAnyWaves = 4;
+
 template <int VEC, bool ANY, int U, int MODE, bool WRAP, bool TL = false>
 __device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, int slice, int lane,
                                            uint64_t *ts = nullptr) {
@@ -457,19 +464,44 @@ __device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, i
     const int j = lane >> a.log_grp;
 
     Acc acc = acc_zero();
+    int slice_row, lead, lead_rows;
+    int64_t items;
+    if constexpr (ANY) {
+        const int part = slice / kAnyWaves, w = slice % kAnyWaves;
+        const int from = w * a.rows_wave / kAnyWaves;
+        const int rows = (w + 1) * a.rows_wave / kAnyWaves - from;
+        slice_row = part * a.rows_wave + from;
+        if constexpr (WRAP) {   // shift < G < cols
+            const int64_t places = (int64_t)rows * a.cols;
+            items = (places + G - 1) >> a.log_grp;
+            const int shift = (int)((items << a.log_grp) - places);
+            lead_rows = shift ? 1 : 0;
+            lead = shift ? a.cols - shift : 0;
+        } else {                // whole rows: G / pitch at a time
+            const int log_rows = a.log_grp - __builtin_ctz(a.pitch);
+            items = (rows + (1 << log_rows) - 1) >> log_rows;
+            lead_rows = (int)(items << log_rows) - rows;
+            lead = 0;
+        }
+    } else {
+        slice_row = slice * a.rows_wave;
+        items = a.items;
+        lead = a.lead;
+        lead_rows = a.lead_rows;
+    }
     // Row and column of the lane's first item, counted from lead_rows above
     // the slice (f * pitch < 2^31: the quotient is exact).
-    const uint32_t f = (uint32_t)(q + a.lead);
+    const uint32_t f = (uint32_t)(q + lead);
     const int r = (int)__umulhi(f << 1, a.pitch_m);
     int col = (int)f - r * a.pitch;
     if (tx0 + j < a.ns && (WRAP || col < a.cols)) {
-        const int shift = a.lead_rows * a.pitch - a.lead;
+        const int shift = lead_rows * a.pitch - lead;
         const bool has_first = q >= shift;
         // The slice's first pixel, at most 2^17 rows of at most 2^17 pixels
         // down; the bases of lanes without a first item may lie above the image.
-        const uint32_t row0 = (uint32_t)(ty * a.NT + slice * a.rows_wave);
+        const uint32_t row0 = (uint32_t)(ty * a.NT + slice_row);
         const uint64_t first = (uint64_t)row0 * (uint32_t)a.N + (uint32_t)(tx0 * a.NT);
-        const int64_t base = (int64_t)first * 4 - (int64_t)((uint32_t)(a.lead_rows * a.N) * 4u);
+        const int64_t base = (int64_t)first * 4 - (int64_t)((uint32_t)(lead_rows * a.N) * 4u);
         const IQA_GLOBAL char *bx = global_bytes(a.x) + base;
         const IQA_GLOBAL char *by = global_bytes(a.y) + base;
         const int over = a.cols * VEC - a.NT;   // ANY: pixels the last quad moves back
@@ -527,7 +559,7 @@ __device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, i
         };
         // Full batches, and the items of the partial one (0..U).
         using Count = std::conditional_t<WRAP, uint64_t, uint32_t>;
-        const Count n = (Count)a.items;
+        const Count n = (Count)items;
         Count left = (n - (shift ? 1 : 0)) / U;
         const int part = (int)(n - left * U);
 
@@ -1172,7 +1204,9 @@ LaunchFn pick_unroll(int unroll, const Want &w) {
 // The instantiated launch shapes: waves 1/2/4/8 with unroll 4/8 and waves 16
 // with unroll 4 for vec 4, and waves 1/4 with unroll 4 for vec 2 and vec 1;
 // each with and without a row split across workgroups.  vec 2 and vec 1 run
-// the any-address quad kernel for NT >= 4 and the narrow loads below that.
+// the any-address quad kernel for NT >= 4, four waves per workgroup whichever
+// is asked for (an odd NT could only ask for one), and the narrow loads below
+// that.
 // Timeline launches exist for the vec 4 shapes, fused mode.
 LaunchFn pick(const iqa_launch_cfg &c, const Want &w) {
     if (c.vec == 4) {
@@ -1186,7 +1220,7 @@ LaunchFn pick(const iqa_launch_cfg &c, const Want &w) {
         }
     }
     if (w.tl || c.unroll != 4 || !(c.waves == 1 || c.waves == 4)) return nullptr;
-    if (w.any) return c.waves == 1 ? pick_shape<4, true, 1, 4>(w) : pick_shape<4, true, 4, 4>(w);
+    if (w.any) return pick_shape<4, true, kAnyWaves, 4>(w);
     if (c.vec == 2) return c.waves == 1 ? pick_shape<2, false, 1, 4>(w) : pick_shape<2, false, 4, 4>(w);
     if (c.vec == 1) return c.waves == 1 ? pick_shape<1, false, 1, 4>(w) : pick_shape<1, false, 4, 4>(w);
     return nullptr;
@@ -1249,26 +1283,25 @@ iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g)
 
 // Built-in launch shape for (N, NT), for shapes the autotuner has not
 // measured: the widest vector the images' alignment and NT allow (vec 2 and
-// vec 1 run any-address quads, one wave per workgroup unless 4 divides NT),
-// four waves per workgroup, and batches of four rows.  Two rules follow.
+// vec 1 run any-address quads), four waves per workgroup, and batches of four
+// rows.  Two rules follow.
 //
 // Lanes per tile.  A wave covers as many adjacent tiles as fit, one row of
-// quads each, unless that leaves too few workgroups or too many items per
-// lane; then it takes fewer tiles and more rows of each.  The lines, in us:
-//   vec 4: 256 workgroups (1000^2/100: 100 workgroups 5.7, 50 6.1; 3000^2/100:
-//          450 workgroups 13.9, 900 14.5), and 8 items where a row is at most
-//          16 quads (3840^2/40: 5 items 21.1, 10 items 21.9).
-//          At 32 lanes a row, two rows if a tile row is whole 128-byte lines
-//          (3840^2/96: 21.0, one row of two tiles 23.3), else one row of two
-//          tiles, which share the line between them (3840^2/120: 20.6, two
-//          rows above 22);
-//   else:  1200 waves (2000^2/50: 1600 waves 8.0, 800 9.0; 8190^2/63: 4290
-//          waves 90.6, 8450 93.1), and 16 items where a row is at most 8
-//          quads (2025^2/25: 11 items 7.9, 22 items 9.1).
+// quads each, unless that leaves less than a workgroup per CU or too many
+// items per lane; then it takes fewer tiles and more rows of each.  The lines,
+// in us: 256 workgroups (1000^2/100: 100 workgroups 5.7, 50 6.1; 3000^2/100:
+// 450 workgroups 13.9, 900 14.5), and 8 items where a row is at most 16 quads
+// (3840^2/40: 5 items 21.1, 10 items 21.9).  At 32 lanes a row, two rows if a
+// tile row is whole 128-byte lines (3840^2/96: 21.0, one row of two tiles
+// 23.3), else one row of two tiles, which share the line between them
+// (3840^2/120: 20.6, two rows above 22).  Any-address quads: 6 items for rows
+// of at most 8 quads (8190^2/30: 4 items 80.0, 8 items 84.0), 16 for rows that
+// nearly fill 16 lanes (2000^2/50: 13 items 8.1, 7 items 8.6; 2025^2/45, 12
+// quads: 6 items 8.5, 12 items 9.7), and two rows at 32 lanes (8190^2/90: 85.8
+// and 88.2).
 //
 // Splits.  A tile whose waves would each make more than 24 items is split over
-// workgroups if the launch has less than one of four waves per CU (or 1500
-// waves): into the fewest parts that give it that, as long as a lane keeps 3
+// workgroups if the launch has less than one of four waves per CU: into the fewest parts that give it that, as long as a lane keeps 3
 // items.  (Unsplit against split: 1000^2/100, 13 items, 5.7 and 6.2;
 // 3000^2/300, 88 items, 23.4 and 15.6.)  Counts from one workgroup per CU to
 // nearly two are passed over: some CUs would have twice the work of others
@@ -1283,41 +1316,39 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     c.unroll = 4;
     c.waves = NT % 4 == 0 ? 4 : 1;
     c.ksplit = 1;
+    int64_t wg_waves = c.waves;
     const bool any = c.vec < 4 && NT >= 4;
     const int64_t cols = any ? (NT + 3) / 4 : NT / c.vec;
     const int64_t row_lanes = std::min<int64_t>(kWave, next_pow2(cols));
     const int64_t ns = N / NT;
-    const int64_t rows = NT / c.waves;     // per wave
+    if (any) wg_waves = kAnyWaves;
+    const int64_t rows = (NT + wg_waves - 1) / wg_waves;   // per wave
     int64_t lanes = row_lanes;
     auto workgroups = [&] { return ns * ((ns * lanes + kWave - 1) / kWave); };
     auto items = [&](int64_t r) {
         return (r * (cols > kWave ? cols : row_lanes) + lanes - 1) / lanes;
     };
     while (lanes < kWave) {
-        const bool few = c.vec == 4 ? workgroups() < 256 : workgroups() * c.waves < 1200;
-        const bool long_lane = row_lanes <= (c.vec == 4 ? 16 : 8) &&
-                               items(rows) > (c.vec == 4 ? 8 : 16);
-        const bool whole_lines = c.vec == 4 && row_lanes == 32 && NT % 32 == 0;
+        const bool few = workgroups() * wg_waves < 1024;
+        const int64_t most = !any ? 8 : row_lanes <= 8 ? 6 : 16 * cols >= 13 * row_lanes ? 16 : 8;
+        const bool long_lane = row_lanes <= 16 && items(rows) > most;
+        const bool whole_lines = row_lanes == 32 && (any || NT % 32 == 0);
         if (!few && !long_lane && !whole_lines) break;
         lanes *= 2;
     }
     c.seg = (int)std::min<int64_t>(lanes, next_pow2(NT / c.vec));
     c.rp = (int)(lanes / c.seg);
     const int64_t tiles = ns * ns;
-    if (workgroups() * c.waves >= (c.waves == 4 ? 1024 : 1500) || items(rows) <= 24 ||
-        lanes < kWave)
-        return c;
-    if (c.vec == 4 && tiles <= 16 && NT % 8 == 0) c.waves = 8;
-    auto enough = [&](int64_t wgs) {
-        return c.waves == 1 ? wgs >= 1500 : wgs >= 225 && (wgs <= 256 || wgs >= 448);
-    };
-    // Parts are equal: divisors of a wave's rows.  At most 4096 slices of a tile
+    if (workgroups() * wg_waves >= 1024 || items(rows) <= 24 || lanes < kWave) return c;
+    if (c.vec == 4 && tiles <= 16 && NT % 8 == 0) c.waves = 8, wg_waves = 8;
+    auto enough = [&](int64_t wgs) { return wgs >= 225 && (wgs <= 256 || wgs >= 448); };
+    // Parts are equal: divisors of a wave's (any: a workgroup's) rows.  At most 4096 slices of a tile
     // (see launch_local) and as many parts in all as the fixed scratch holds.
     constexpr int64_t kMostParts = (IQA_NOALLOC_SCRATCH_BYTES - (64 << 10)) / 16;
     const int32_t per = (int32_t)(NT / c.waves);
-    for (int32_t ks = 1; ks <= per && ks * c.waves <= 4096 && tiles * ks <= kMostParts; ++ks) {
+    for (int32_t ks = 1; ks <= per && ks * wg_waves <= 4096 && tiles * ks <= kMostParts; ++ks) {
         if (per % ks != 0) continue;
-        if (items(per / ks) < 3) break;
+        if (items((NT / ks + wg_waves - 1) / wg_waves) < 3) break;
         c.ksplit = ks;
         if (enough(tiles * ks)) break;
     }
@@ -1565,17 +1596,19 @@ void fill_pair(PairArgs &a, const float *x, const float *y, int64_t N, int64_t N
     a.ngx = (int32_t)g.ngx;
     a.ngx_m = div_magic(g.ngx);
     a.log_grp = g.log_grp;
-    a.rows_wave = (int32_t)(NT / ((int64_t)c.waves * c.ksplit));
+    a.rows_wave = (int32_t)(NT / ((g.any ? 1 : (int64_t)c.waves) * c.ksplit));
     const int64_t lanes = int64_t(1) << g.log_grp;
     const int64_t pitch = g.wrap ? g.cols : next_pow2(g.cols);
     a.cols = g.cols;
     a.pitch = (int32_t)pitch;
     a.pitch_m = (uint32_t)(((int64_t(1) << 31) + pitch - 1) / pitch);
-    const int64_t places = a.rows_wave * pitch;
-    a.items = (places + lanes - 1) / lanes;
-    const int64_t shift = a.items * lanes - places;
-    a.lead_rows = (int32_t)((shift + pitch - 1) / pitch);
-    a.lead = (int32_t)(a.lead_rows * pitch - shift);
+    if (!g.any) {
+        const int64_t places = a.rows_wave * pitch;
+        a.items = (places + lanes - 1) / lanes;
+        const int64_t shift = a.items * lanes - places;
+        a.lead_rows = (int32_t)((shift + pitch - 1) / pitch);
+        a.lead = (int32_t)(a.lead_rows * pitch - shift);
+    }
     const int64_t quad_bytes = 4 * (g.any ? 4 : c.vec);
     a.step = (int32_t)(g.wrap ? lanes * quad_bytes : lanes / pitch * N * 4);
 }
@@ -1590,12 +1623,16 @@ hipError_t launch_combine(const KArgs &a, int mode, const Geometry &g, hipStream
 // LDS of a tiles_local_kernel workgroup: 16 bytes per slice of its tile.
 constexpr size_t kLocalLdsMax = 64 << 10;
 
-size_t local_lds(const iqa_launch_cfg &c) { return (size_t)c.waves * c.ksplit * sizeof(float4); }
+int part_slices(const iqa_launch_cfg &c, const Geometry &g) { return g.any ? kAnyWaves : c.waves; }
+
+size_t local_lds(const iqa_launch_cfg &c, const Geometry &g) {
+    return (size_t)part_slices(c, g) * c.ksplit * sizeof(float4);
+}
 
 // Shapes whose default launch splits without split_needs_prepare: whether this
 // configuration can run without a workspace too.
 bool local_ok(const iqa_launch_cfg &c, const Geometry &g) {
-    return g.ht == 1 && c.unroll == 4 && (c.vec == 4 || g.any) && local_lds(c) <= kLocalLdsMax &&
+    return g.ht == 1 && c.unroll == 4 && (c.vec == 4 || g.any) && local_lds(c, g) <= kLocalLdsMax &&
            (c.waves == 1 || c.waves == 4 || c.waves == 8);
 }
 
@@ -1605,7 +1642,8 @@ hipError_t launch_local_mode(const KArgs &a, int mode, const iqa_launch_cfg &c, 
     void (*fn)(KArgs, int) = mode == kLisi  ? &tiles_local_kernel<ANY, 4, kLisi, WRAP>
                              : mode == kAug ? &tiles_local_kernel<ANY, 4, kAug, WRAP>
                                             : &tiles_local_kernel<ANY, 4, kBoth, WRAP>;
-    return launch_with_lds(fn, (unsigned)g.groups, kLocalWaves * kWave, local_lds(c), s, a, c.waves);
+    return launch_with_lds(fn, (unsigned)g.groups, kLocalWaves * kWave, local_lds(c, g), s, a,
+                           part_slices(c, g));
 }
 
 hipError_t launch_local(const KArgs &a, int mode, const iqa_launch_cfg &c, const Geometry &g,
