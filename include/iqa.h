@@ -255,8 +255,8 @@ iqa_status iqa_tune_set(int64_t N, int64_t NT, int kind, const iqa_launch_cfg *c
  * measurements stay). */
 void iqa_tune_clear(void);
 
-/* Persistent wave count the autotuner found best for iqa_tiles_batched on
- * this GPU (2048 when no measurement is compiled in). */
+/* Most waves per launch found best for iqa_tiles_batched on this GPU (2048
+ * when no measurement is compiled in). */
 int64_t iqa_batch_default_waves(void);
 
 /* ------------------------------------------------------------------------ */
@@ -308,9 +308,10 @@ iqa_status iqa_batch_describe(const iqa_pair *pairs, int64_t count, void *descs,
 /* One persistent launch over every pair of a described batch.
  *   descs_dev    device copy of the descriptors from iqa_batch_describe.
  *   count, total_units  as given to / returned by iqa_batch_describe.
- *   waves        persistent waves (multiple of 4; 2048 = 8 per CU is a good
- *                start): the launch has G = min(waves/4, total_units)
- *                workgroups, and workgroup b processes units b, b+G, b+2G, ...
+ *   waves        most waves of the launch (multiple of 4): waves/4 workgroups
+ *                share the units, or one workgroup per unit if there are fewer
+ *                units than that (a few more run empty).  Which workgroup takes
+ *                a unit has no effect on results.
  * Allocates nothing and calls nothing but the launch, so it can be captured
  * into a HIP graph.  The descriptor contents are not validated on the device:
  * pass exactly what iqa_batch_describe wrote, and a device buffer that holds

@@ -912,10 +912,9 @@ __global__ __launch_bounds__(kWave) void combine_kernel(KArgs a) {
 //   * a pair whose geometry has kBatchWaves waves per tile group gives each
 //     tile group a unit of its own: the waves take its row slices and combine
 //     them in LDS exactly as tiles_kernel does.
-// A persistent grid takes units round-robin: workgroup b does units b, b + G,
-// b + 2G, ... where G is the number of workgroups.  Either way a pair's
-// results are bitwise equal to a single-pair launch with the same geometry
-// and unroll (ksplit 1).
+// A grid smaller than the units is persistent (see unit_chunk_log).  Either way
+// a pair's results are bitwise equal to a single-pair launch with the same
+// geometry and unroll (ksplit 1).
 struct BatchDesc {
     PairArgs a;
     int64_t unit_begin;
@@ -938,12 +937,37 @@ __host__ __device__ __forceinline__ int64_t batch_units(const PairArgs &a) {
     return batch_coop(a) ? groups : (groups + kBatchWaves - 1) / kBatchWaves;
 }
 
+// How units are dealt to the XCDs: chunks of 2^unit_chunk_log consecutive units
+// go to the eight of them in turn, so that each gets its share of every pair,
+// and an XCD's workgroups take its units in turn.  (One contiguous range of
+// workgroups per XCD, as in the tile kernel, gave the second round of units to
+// one XCD: 30 ragged pairs, 1.2 GB, 245 us against 184; and units of unequal
+// cost, 203 against 180.)  Chunks keep neighbouring tile groups, which share
+// lines and DRAM pages, on one XCD: 128 units where there are enough (four
+// 4096^2/128 pairs, 4096 units: chunks of 128 units 86.8 us, 64 90.0, 16 91.6),
+// else a 32nd of all units, at most 32 (512 pairs of 256^2/32, 2048 units:
+// 46.2 with 32, 48.6 with 64).
+__host__ __device__ __forceinline__ int unit_chunk_log(int64_t units) {
+    if (units >= 4096) return 7;
+    int r = 0;
+    while (r < 5 && (int64_t(64) << r) <= units) ++r;
+    return r;
+}
+
 template <int U>
 __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, int64_t units) {
     __shared__ float4 lds[kBatchWaves][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (int64_t u = xcd_remap(blockIdx.x, gridDim.x); u < units; u += gridDim.x) {
+    const int log_chunk = unit_chunk_log(units);
+    const uint32_t xcds = gridDim.x < kXcds ? gridDim.x : kXcds;
+    const uint32_t xcd = blockIdx.x % xcds;
+    const uint32_t stride = gridDim.x / xcds + (xcd < gridDim.x % xcds ? 1 : 0);
+    for (int64_t i = blockIdx.x / xcds;; i += stride) {
+        const int64_t first = ((i >> log_chunk) * xcds + xcd) << log_chunk;
+        if (first >= units) break;
+        const int64_t u = first + (i & ((1 << log_chunk) - 1));
+        if (u >= units) continue;
         // Binary search for the pair whose units contain u (same in every wave).
         int lo = 0, hi = count - 1;
         while (lo < hi) {
@@ -1000,10 +1024,13 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
     }
 }
 
-// The descriptor table in device memory (any number of pairs).
+// The descriptor table in device memory (any number of pairs).  Bound by HBM: 30
+// ragged pairs (1.2 GB) run at 6.6 TB/s, 256 at 6.8, a plain read at 6.9.  Three
+// waves per SIMD: more waves with fewer loads each in flight are slower on mixed
+// batches (loads in batches of four, five waves: 223 us against 184 for the 30).
 template <int U>
-__global__ __launch_bounds__(kBatchWaves * kWave) void batch_kernel(const BatchDesc *descs,
-                                                                    int count, int64_t units) {
+__global__ __launch_bounds__(kBatchWaves * kWave, 3) void batch_kernel(const BatchDesc *descs,
+                                                                       int count, int64_t units) {
     batch_body<U>(descs, count, units);
 }
 
@@ -1440,20 +1467,20 @@ iqa_launch_cfg pick_cfg(int64_t N, int64_t NT, const float *x, const float *y) {
     return default_cfg(N, NT, x, y);
 }
 
-// Per-pair geometry inside a batch: vec 4, one wave per tile group, no row
-// split, and as many tiles per wave as make a unit of about 64 KiB of input.
-
+// Per-pair geometry inside a batch: units of about 128 KiB of input, so that a
+// batch's units cost alike whatever its shapes: four tile groups of one wave
+// each for small tiles, one group whose rows four waves share for larger ones.
 iqa_launch_cfg batch_cfg(int64_t N, int64_t NT) {
     iqa_launch_cfg c;
     if (tuned_lookup(N, NT, 1, &c)) return c;
     c.vec = 4;
-    c.waves = 1;
+    c.waves = NT <= 40 ? 1 : kBatchWaves;
     c.unroll = kBatchUnroll;
     c.ksplit = 1;
     const int64_t lpt = NT / 4;
     c.seg = (int)std::min<int64_t>(kWave, next_pow2(lpt));
     const int64_t tpw = kWave / c.seg;
-    const int64_t want = std::max<int64_t>(1, (int64_t(64) << 10) / (8 * NT * NT));
+    const int64_t want = (int64_t(32) << 10) * c.waves / (8 * NT * NT);
     int64_t ht = 1;
     while (ht * 2 <= tpw && ht * 2 <= want && ht * 2 <= next_pow2(N / NT)) ht *= 2;
     c.rp = (int)(tpw / ht);
@@ -1750,6 +1777,15 @@ iqa_status check_outputs_params(float *lisi, float *auglisi, float *sums, float 
     return IQA_OK;
 }
 
+// Workgroups of a batch launch: as many as `waves` gives, but no more than one
+// per unit of each XCD's share.
+int64_t batch_grid(int64_t waves, int64_t units) {
+    const int log_chunk = unit_chunk_log(units);
+    const int64_t chunks = (units + (int64_t(1) << log_chunk) - 1) >> log_chunk;
+    const int64_t all = ((chunks + kXcds - 1) / kXcds * kXcds) << log_chunk;
+    return std::min(waves / kBatchWaves, chunks < kXcds ? units : all);
+}
+
 template <int CAP>
 iqa_status launch_inline(const void *descs_host, int64_t count, int64_t total_units,
                          int64_t blocks, hipStream_t s) {
@@ -1961,7 +1997,7 @@ iqa_status iqa_tiles_batched(const void *descs_dev, int64_t count, int64_t total
     if (!aligned(descs_dev, 16)) return IQA_ERR_ALIGN;
     if (waves < kBatchWaves || waves % kBatchWaves != 0 || waves / kBatchWaves > INT_MAX)
         return IQA_ERR_CONFIG;
-    const int64_t blocks = std::min<int64_t>(waves / kBatchWaves, total_units);
+    const int64_t blocks = batch_grid(waves, total_units);
     return hip_status(launch_kernel(&batch_kernel<kBatchUnroll>, (unsigned)blocks,
                                     kBatchWaves * kWave, static_cast<hipStream_t>(stream),
                                     static_cast<const BatchDesc *>(descs_dev), (int)count,
@@ -1984,7 +2020,7 @@ iqa_status iqa_tiles_batched_inline(const void *descs_host, int64_t count, int64
         next += batch_units(d.a);
     }
     if (next != total_units) return IQA_ERR_CONFIG;
-    const int64_t blocks = std::min<int64_t>(waves / kBatchWaves, total_units);
+    const int64_t blocks = batch_grid(waves, total_units);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (count == 1) return launch_inline<1>(descs_host, count, total_units, blocks, s);
     if (count <= 4) return launch_inline<4>(descs_host, count, total_units, blocks, s);
