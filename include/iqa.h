@@ -229,9 +229,24 @@ iqa_status iqa_prepare(int64_t N, int64_t NT, const iqa_launch_cfg *cfg, void *s
  * Eq. 3/4 weight each child's index by its own denominator, which equals
  * adding the children's sums and applying Eq. 1/2 to the totals; the kernel
  * does the latter (Kahan-compensated, fixed order) and so avoids the
- * cancellation of reconstructing sums from rounded indices. */
+ * cancellation of reconstructing sums from rounded indices.  Large f runs over
+ * several workgroups per parent with a buffer per (device, stream) like split
+ * tiles, but none of their rules: captured, or without memory to be had, one
+ * workgroup per parent does the same, bitwise. */
 iqa_status iqa_merge_tiles(const float *sums_in, int64_t ns, int64_t f, float D, float C2,
                            float C, float *lisi, float *auglisi, float *sums_out, void *stream);
+
+/* The next `levels` levels of a pyramid at once: level l (0-based) merges 2 x 2
+ * tiles of the level before it, the first those of `sums_in` (ns tiles per
+ * side; 2^levels divides ns), so it has (ns >> (l+1))^2 tiles.
+ *   lisi, auglisi, sums_out  host arrays of `levels` device pointers, each as
+ *             in iqa_merge_tiles for its level (nullable, one non-NULL per
+ *             level; the sums of every sixth level only if it is the last).
+ * Bitwise the chain of iqa_merge_tiles calls with f == 2, in one launch per six
+ * levels; uses no workspace. */
+iqa_status iqa_pyramid(const float *sums_in, int64_t ns, int64_t levels, float D, float C2, float C,
+                       float *const *lisi, float *const *auglisi, float *const *sums_out,
+                       void *stream);
 
 /* ------------------------------------------------------------------------ */
 /* Tuned launch shapes                                                       */

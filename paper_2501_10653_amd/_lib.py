@@ -149,6 +149,8 @@ def load() -> ctypes.CDLL:
         "iqa_wall_clock_khz": ([], i64),
         "iqa_read_ceiling": ([vp, i64, vp, i64, vp], ctypes.c_int),
         "iqa_merge_tiles": ([vp, i64, i64, f, f, f, vp, vp, vp, vp], ctypes.c_int),
+        "iqa_pyramid": ([vp, i64, i64, f, f, f, ctypes.POINTER(vp), ctypes.POINTER(vp),
+                         ctypes.POINTER(vp), vp], ctypes.c_int),
         "iqa_tune_set": ([i64, i64, ctypes.c_int, cfgp], ctypes.c_int),
         "iqa_tune_clear": ([], None),
         "iqa_batch_default_waves": ([], ctypes.c_int64),

@@ -1058,10 +1058,8 @@ __global__ __launch_bounds__(kBatchWaves * kWave) void batch_kernel_inline(Inlin
 // Eq. 3 and Eq. 4 recover the value of a larger tile (or of the whole image)
 // from its child tiles.  Both weight each child's index by its own
 // denominator, which is the same as adding the children's sums A, P, Sx, Sy
-// and applying Eq. 1 / Eq. 2 to the totals; that is what this kernel does,
-// from the sums iqa_tiles exports.  One workgroup per parent tile: each thread
-// adds a fixed stride of children with Kahan compensation, the wave and the
-// workgroup then add in a fixed order, and thread 0 finalises.
+// and applying Eq. 1 / Eq. 2 to the totals; that is what these kernels do, from
+// the sums iqa_tiles exports.
 struct MergeArgs {
     const float *sums_in;   // ns*ns children, 4 floats each
     int64_t ns;             // children per side
@@ -1070,40 +1068,221 @@ struct MergeArgs {
     float *lisi;
     float *aug;
     float *sums;
+    int32_t parts;          // workgroups per parent
+    float *ws;              // parts > 1: their partial sums and the parents' counters
 };
 
-__global__ __launch_bounds__(256) void merge_kernel(MergeArgs m) {
-    const int64_t np = m.ns / m.f;
-    const int64_t p = blockIdx.x;
-    const int64_t py = p / np, px = p - py * np;
-    const int64_t nchild = m.f * m.f;
-    Acc acc = acc_zero();
-    const float4 *in = reinterpret_cast<const float4 *>(m.sums_in);
-    for (int64_t c = threadIdx.x; c < nchild; c += 256) {
-        const int64_t cy = c / m.f, cx = c - cy * m.f;
-        const float4 v = in[(py * m.f + cy) * m.ns + px * m.f + cx];
-        cadd(acc.A, v.x);
-        cadd(acc.P, v.y);
-        cadd(acc.X, v.z);
-        cadd(acc.Y, v.w);
-    }
-    Sum4 s = group_allreduce<kBoth>(fold(acc), 6);
-    __shared__ float4 part[4];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    if (lane == 0) part[wave] = float4{s.A, s.P, s.X, s.Y};
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    const float4 a = part[0], b = part[1], c = part[2], d = part[3];
-    const Sum4 t{(a.x + b.x) + (c.x + d.x), (a.y + b.y) + (c.y + d.y),
-                 (a.z + b.z) + (c.z + d.z), (a.w + b.w) + (c.w + d.w)};
+__device__ __forceinline__ void finalize_merge(float D, float C2, float C, float *lisi, float *aug,
+                                               float *sums, int64_t t, const Sum4 &s) {
     PairArgs k{};
-    k.D = m.D;
-    k.C2 = m.C2;
-    k.C = m.C;
-    k.lisi = m.lisi;
-    k.aug = m.aug;
-    k.sums = m.sums;
-    finalize<kBoth>(k, p, t);
+    k.D = D;
+    k.C2 = C2;
+    k.C = C;
+    k.lisi = lisi;
+    k.aug = aug;
+    k.sums = sums;
+    finalize<kBoth>(k, t, s);
+}
+
+// f from 3 to 16: 2^log_g lanes per parent and LOADS children each, so a wave
+// merges 64 >> log_g parents: one child per lane to f = 8, then a wave with four.
+// (A workgroup per parent took 4.4 us for 48^2 parents of 4^2 children, where
+// this is launch-bound; and 4.9 us for 32^2 of 16^2, 4.1 here.)
+constexpr int kMergeThreads = 256;
+
+template <int LOADS>
+__global__ __launch_bounds__(kMergeThreads) void merge_small_kernel(MergeArgs m, int log_g) {
+    const int np = (int)(m.ns / m.f), f = (int)m.f;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int q = lane & ((1 << log_g) - 1);
+    const int p = (int)(((int64_t)blockIdx.x * kMergeThreads + threadIdx.x) >> log_g);
+    if (p >= np * np) return;   // the whole group
+    const int py = p / np, px = p - py * np;
+    const float4 *in =
+        reinterpret_cast<const float4 *>(m.sums_in) + ((int64_t)py * m.ns + px) * f;
+    float4 v[LOADS];
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+        const int c = q + u * kWave, cy = c / f, cx = c - cy * f;
+        v[u] = c < f * f ? in[cy * m.ns + cx] : float4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float4 w = wave_tree<LOADS>(v);
+    const Sum4 s = group_allreduce<kBoth>(Sum4{w.x, w.y, w.z, w.w}, log_g);
+    if (q == 0) finalize_merge(m.D, m.C2, m.C, m.lisi, m.aug, m.sums, p, s);
+}
+
+// f above 16.  A parent's children are cut into `parts` runs of
+// part_children(), each added by kMergeThreads threads: a thread Kahan-adds
+// every kMergeThreads-th child of the run, with eight loads in flight, the lanes
+// and the four waves then add in a fixed order.  The runs' sums are added as
+// combine_parts adds a split tile's: lane by lane with Kahan compensation, then
+// over the wave.  (One run of any length took 393 us for the whole of a 512^2
+// level, 4 MiB on one CU with one load in flight per thread.)
+__host__ __device__ __forceinline__ int64_t part_children(int64_t f, int64_t parts) {
+    return ((f * f + parts - 1) / parts + kMergeThreads - 1) / kMergeThreads * kMergeThreads;
+}
+
+// Thread t's share of run `part` of parent p, summed over its wave.
+__device__ __forceinline__ float4 merge_run(const MergeArgs &m, int64_t p, int part, int t) {
+    const int64_t np = m.ns / m.f;
+    const int64_t py = p / np, px = p - py * np;
+    const int64_t run = part_children(m.f, m.parts);
+    const int64_t end = (part + 1) * run < m.f * m.f ? (part + 1) * run : m.f * m.f;
+    const float4 *in =
+        reinterpret_cast<const float4 *>(m.sums_in) + (py * m.ns + px) * m.f;
+    int64_t c = part * run + t;
+    int64_t cy = c / m.f, cx = c - cy * m.f;
+    const int64_t dy = kMergeThreads / m.f, dx = kMergeThreads - dy * m.f;
+    Acc acc = acc_zero();
+    constexpr int kLoads = 8;
+    for (int64_t left = run; left > 0; left -= kLoads * kMergeThreads) {
+        float4 v[kLoads];
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            if (u * kMergeThreads >= left) break;   // the same for every thread
+            v[u] = c < end ? in[cy * m.ns + cx] : float4{0.f, 0.f, 0.f, 0.f};
+            c += kMergeThreads;
+            cx += dx;
+            cy += dy;
+            if (cx >= m.f) {
+                cx -= m.f;
+                ++cy;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            if (u * kMergeThreads >= left) break;
+            cadd(acc.A, v[u].x);
+            cadd(acc.P, v[u].y);
+            cadd(acc.X, v[u].z);
+            cadd(acc.Y, v[u].w);
+        }
+    }
+    const Sum4 s = group_allreduce<kBoth>(fold(acc), 6);
+    return float4{s.A, s.P, s.X, s.Y};
+}
+
+// The runs' sums of one parent, added by one wave.
+template <typename Run>
+__device__ __forceinline__ void merge_runs(const MergeArgs &m, int64_t p, int lane, Run run) {
+    Acc c = acc_zero();
+    for (int i = lane; i < m.parts; i += kWave) {
+        const float4 w = run(i);
+        cadd(c.A, w.x);
+        cadd(c.P, w.y);
+        cadd(c.X, w.z);
+        cadd(c.Y, w.w);
+    }
+    const Sum4 s = group_allreduce<kBoth>(fold(c), 6);
+    if (lane == 0) finalize_merge(m.D, m.C2, m.C, m.lisi, m.aug, m.sums, p, s);
+}
+
+// One workgroup per run; the last of a parent's to finish adds them (the ticket
+// of split_finish, one counter and one line per run and parent).
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeArgs m) {
+    __shared__ float4 waves[kMergeThreads / kWave];
+    const int64_t p = blockIdx.x / m.parts;
+    const int part = (int)(blockIdx.x - p * m.parts);
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const float4 v = merge_run(m, p, part, threadIdx.x);
+    if (lane == 0) waves[wave] = v;
+    __syncthreads();
+    if (wave != 0) return;
+    float4 w[4] = {waves[0], waves[1], waves[2], waves[3]};
+    const float4 t = wave_tree<4>(w);
+    if (m.parts == 1) {
+        if (lane == 0)
+            finalize_merge(m.D, m.C2, m.C, m.lisi, m.aug, m.sums, p, Sum4{t.x, t.y, t.z, t.w});
+        return;
+    }
+    float4 *slots = reinterpret_cast<float4 *>(m.ws) + p * m.parts * (kLine / 16);
+    if (lane == 0) store_coherent(slots + part * (kLine / 16), t);
+    uint32_t *cnt = reinterpret_cast<uint32_t *>(m.ws) - (kLine / 4) * (p + 1);
+    wait_vmem();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    uint32_t ticket = 0;
+    if (lane == 0)
+        ticket = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ticket = __builtin_amdgcn_readfirstlane(ticket);
+    if (ticket != (uint32_t)(m.parts - 1)) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    merge_runs(m, p, lane, [&](int i) { return load_coherent(slots + i * (kLine / 16)); });
+    if (lane == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// All runs of a parent in one workgroup, four at a time, where there is no
+// workspace (under capture); the same bits.
+constexpr int kMergeLocalThreads = 4 * kMergeThreads;
+
+__global__ __launch_bounds__(kMergeLocalThreads) void merge_local_kernel(MergeArgs m) {
+    extern __shared__ float4 waves[];   // [parts][4]
+    const int lane = threadIdx.x & (kWave - 1);
+    const int team = threadIdx.x / kMergeThreads, t = threadIdx.x % kMergeThreads;
+    for (int part = team; part < m.parts; part += kMergeLocalThreads / kMergeThreads) {
+        const float4 v = merge_run(m, blockIdx.x, part, t);
+        if (lane == 0) waves[part * 4 + t / kWave] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    merge_runs(m, blockIdx.x, lane, [&](int i) {
+        float4 w[4] = {waves[i * 4], waves[i * 4 + 1], waves[i * 4 + 2], waves[i * 4 + 3]};
+        return wave_tree<4>(w);
+    });
+}
+
+// A pyramid's next levels (f = 2 each) from one level's sums: a workgroup takes
+// a block of 64 x 64 tiles and merges it up to six times, the levels' sums
+// passing through LDS, so a level is read once and written once and a whole
+// pyramid is one or two launches.  A parent is ((c00 + c01) + (c10 + c11)), as
+// merge_small_kernel's lanes add four children.  (Seven levels over 192^2 tiles
+// as merges of their own took 29 us on the GPU and 12 us of host time each.)
+constexpr int kPyramidLevels = 6;
+constexpr int kPyramidThreads = 1024;   // one per parent of the first level
+
+struct PyramidArgs {
+    const float *sums_in;   // ns*ns tiles, 4 floats each
+    int32_t ns;             // tiles per side, a multiple of 2^levels
+    int32_t levels;         // 1..kPyramidLevels
+    int32_t nbx;            // blocks per side: ceil(ns / 64)
+    float D, C2, C;
+    float *lisi[kPyramidLevels];
+    float *aug[kPyramidLevels];
+    float *sums[kPyramidLevels];
+};
+
+__global__ __launch_bounds__(kPyramidThreads) void pyramid_kernel(PyramidArgs a) {
+    __shared__ float4 level[kPyramidThreads];
+    const int by = blockIdx.x / a.nbx, bx = blockIdx.x - by * a.nbx;
+    int side = 32, n = a.ns / 2;   // parents per side: of the block, of the level
+    int ty = threadIdx.x >> 5, tx = threadIdx.x & 31;
+    auto add = [](const float4 &p, const float4 &q) {
+        return float4{p.x + q.x, p.y + q.y, p.z + q.z, p.w + q.w};
+    };
+    for (int l = 0; l < a.levels; ++l) {
+        const int py = by * side + ty, px = bx * side + tx;
+        const bool mine = (int)threadIdx.x < side * side && py < n && px < n;
+        float4 v{0.f, 0.f, 0.f, 0.f};
+        if (mine) {
+            if (l == 0) {
+                const float4 *c = reinterpret_cast<const float4 *>(a.sums_in) +
+                                  (int64_t)(2 * py) * a.ns + 2 * px;
+                v = add(add(c[0], c[1]), add(c[a.ns], c[a.ns + 1]));
+            } else {
+                const float4 *c = level + (2 * ty) * (2 * side) + 2 * tx;
+                v = add(add(c[0], c[1]), add(c[2 * side], c[2 * side + 1]));
+            }
+            finalize_merge(a.D, a.C2, a.C, a.lisi[l], a.aug[l], a.sums[l], (int64_t)py * n + px,
+                           Sum4{v.x, v.y, v.z, v.w});
+        }
+        if (l + 1 == a.levels) break;   // the same for every thread
+        __syncthreads();                // the level below has been read
+        if ((int)threadIdx.x < side * side) level[threadIdx.x] = v;
+        __syncthreads();
+        side /= 2;
+        n /= 2;
+        ty = threadIdx.x / side;
+        tx = threadIdx.x % side;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1539,6 +1718,13 @@ SplitNeed split_need(const Geometry &g, const iqa_launch_cfg &c) {
 
 size_t round_up(size_t v, size_t m) { return (v + m - 1) / m * m; }
 
+// Whether s is being captured (or cannot say).
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (s == nullptr) return false;
+    return hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
 // *part receives the partial-sum region; the counter region ends where it
 // starts.  `own`: the buffer of the default launches that never use a
 // workspace under capture.  The caller holds g_ws_mutex.
@@ -1557,7 +1743,12 @@ iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float *
         const size_t cb = round_up(std::max(need.cnt_bytes, w.cnt_bytes), 4096);
         const size_t pb = round_up(std::max(need.part_bytes, w.part_bytes), 4096);
         void *p = nullptr;
+        // A launch that needs no preparation may come while another stream is
+        // being captured: the allocation must not disturb that.
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (own) (void)hipThreadExchangeStreamCaptureMode(&mode);
         e = hipMalloc(&p, cb + pb);
+        if (own) (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (e != hipSuccess) return hip_status(e);
         e = hipMemsetAsync(p, 0, cb + pb, s);
         if (e != hipSuccess) {
@@ -1718,13 +1909,7 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
     bool own = false, local = false;
     if (c.ksplit > 1 && !cfg_in && local_ok(c, g) && !tuned_or_prepared(N, NT, c, x, y)) {
         own = true;
-        local = ws == Ws::kScratch;
-        if (ws == Ws::kLibrary && s != nullptr) {
-            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            const hipError_t e = hipStreamIsCapturing(s, &cs);
-            if (e != hipSuccess) return hip_status(e);
-            local = cs != hipStreamCaptureStatusNone;
-        }
+        local = ws == Ws::kScratch || (ws == Ws::kLibrary && capturing(s));
     }
     // The workspace (or scratch) stays locked until the launches are
     // enqueued: a combine-mode split is two launches, and another host
@@ -1744,7 +1929,12 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
         } else {
             ws_lock.lock();
             st = workspace_for(s, own, need, &a.ws);
-            if (st != IQA_OK) return st;
+            if (st != IQA_OK && !own) return st;
+            if (st != IQA_OK) {   // no memory to be had: do without
+                (void)hipGetLastError();
+                ws_lock.unlock();
+                local = true;
+            }
         }
     }
     if (ws == Ws::kPrepare) return IQA_OK;
@@ -1757,6 +1947,65 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
     hipError_t e = fn(a, tl, (unsigned)g.grid, s);
     if (e == hipSuccess && a.smode == kSplitCombine) e = launch_combine(a, mode, g, s);
     return hip_status(e);
+}
+
+// One level of merging.  Which kernel, and in how many runs, is a function of
+// (ns, f) alone.  f == 2 is a pyramid of one level: one thread per parent (a
+// workgroup each took 42 us for 256^2 parents).  Runs of 4096 children, as long
+// as the launch has fewer than 1024 workgroups: 16 loads per thread, below which
+// the ticket costs more than it saves.
+constexpr int64_t kRunChildren = 4096, kMergeMaxGrid = 1024;
+
+iqa_status merge(const float *sums_in, int64_t ns, int64_t f, float D, float C2, float C,
+                 float *lisi, float *aug, float *sums, hipStream_t s) {
+    const int64_t parents = (ns / f) * (ns / f);
+    if (f == 2) {
+        PyramidArgs a{};
+        a.sums_in = sums_in;
+        a.ns = (int32_t)ns;
+        a.levels = 1;
+        a.nbx = (int32_t)((ns + 63) / 64);
+        a.D = D;
+        a.C2 = C2;
+        a.C = C;
+        a.lisi[0] = lisi;
+        a.aug[0] = aug;
+        a.sums[0] = sums;
+        return hip_status(
+            launch_kernel(&pyramid_kernel, (unsigned)(a.nbx * a.nbx), kPyramidThreads, s, a));
+    }
+    MergeArgs m{sums_in, ns, f, D, C2, C, lisi, aug, sums, 1, nullptr};
+    if (f <= 16) {
+        const int log_g = std::min(ilog2(f * f), 6);
+        const int64_t per = kMergeThreads >> log_g;
+        return hip_status(launch_kernel(f <= 8 ? &merge_small_kernel<1> : &merge_small_kernel<4>,
+                                        (unsigned)((parents + per - 1) / per), kMergeThreads, s, m,
+                                        log_g));
+    }
+    m.parts = (int32_t)std::max<int64_t>(
+        1, std::min((f * f + kRunChildren - 1) / kRunChildren, kMergeMaxGrid / parents));
+    m.parts = (int32_t)((f * f + part_children(f, m.parts) - 1) / part_children(f, m.parts));
+    if (m.parts == 1)
+        return hip_status(launch_kernel(&merge_kernel, (unsigned)parents, kMergeThreads, s, m));
+    std::unique_lock<std::mutex> lock(g_ws_mutex, std::defer_lock);
+    bool local = capturing(s);
+    if (!local) {
+        SplitNeed need;
+        need.cnt_bytes = (size_t)(parents * kLine);
+        need.part_bytes = (size_t)(parents * m.parts * kLine);
+        lock.lock();
+        if (workspace_for(s, true, need, &m.ws) != IQA_OK) {
+            (void)hipGetLastError();
+            lock.unlock();
+            local = true;
+        }
+    }
+    if (local)
+        return hip_status(launch_with_lds(&merge_local_kernel, (unsigned)parents,
+                                          kMergeLocalThreads, (size_t)m.parts * 4 * sizeof(float4),
+                                          s, m));
+    return hip_status(launch_kernel(&merge_kernel, (unsigned)(parents * m.parts), kMergeThreads, s,
+                                    m));
 }
 
 iqa_status check_common(const float *x, const float *y, int64_t N, int64_t NT) {
@@ -2036,9 +2285,44 @@ iqa_status iqa_merge_tiles(const float *sums_in, int64_t ns, int64_t f, float D,
     if (!aligned(sums_in, 16)) return IQA_ERR_ALIGN;
     const int64_t np = ns / f;
     if (np * np > INT_MAX) return IQA_ERR_SHAPE;
-    MergeArgs m{sums_in, ns, f, D, C2, C, lisi, auglisi, sums_out};
-    return hip_status(launch_kernel(&merge_kernel, (unsigned)(np * np), 256,
-                                    static_cast<hipStream_t>(stream), m));
+    return merge(sums_in, ns, f, D, C2, C, lisi, auglisi, sums_out,
+                 static_cast<hipStream_t>(stream));
+}
+
+iqa_status iqa_pyramid(const float *sums_in, int64_t ns, int64_t levels, float D, float C2, float C,
+                       float *const *lisi, float *const *auglisi, float *const *sums_out,
+                       void *stream) {
+    if (!sums_in) return IQA_ERR_NULL;
+    if (ns <= 0 || ns > IQA_MAX_N || levels < 1 || levels > 17 || ns % (int64_t(1) << levels) != 0)
+        return IQA_ERR_SHAPE;
+    if (!lisi || !auglisi || !sums_out) return IQA_ERR_NULL;
+    if (!aligned(sums_in, 16)) return IQA_ERR_ALIGN;
+    for (int64_t l = 0; l < levels; ++l) {
+        const iqa_status st = check_outputs_params(lisi[l], auglisi[l], sums_out[l], D, 1.f, C2, C);
+        if (st != IQA_OK) return st;
+        // The sums of every sixth level feed the next launch.
+        if ((l + 1) % kPyramidLevels == 0 && l + 1 < levels && !sums_out[l]) return IQA_ERR_NULL;
+    }
+    for (int64_t l = 0; l < levels; l += kPyramidLevels) {
+        PyramidArgs a{};
+        a.sums_in = l ? sums_out[l - 1] : sums_in;
+        a.ns = (int32_t)(ns >> l);
+        a.levels = (int32_t)std::min<int64_t>(kPyramidLevels, levels - l);
+        a.nbx = (a.ns + 63) / 64;
+        a.D = D;
+        a.C2 = C2;
+        a.C = C;
+        for (int i = 0; i < a.levels; ++i) {
+            a.lisi[i] = lisi[l + i];
+            a.aug[i] = auglisi[l + i];
+            a.sums[i] = sums_out[l + i];
+        }
+        const iqa_status st =
+            hip_status(launch_kernel(&pyramid_kernel, (unsigned)(a.nbx * a.nbx), kPyramidThreads,
+                                     static_cast<hipStream_t>(stream), a));
+        if (st != IQA_OK) return st;
+    }
+    return IQA_OK;
 }
 
 iqa_status iqa_read_ceiling(const float *buf, int64_t n, float *out, int64_t blocks,

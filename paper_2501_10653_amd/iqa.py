@@ -287,10 +287,26 @@ def pyramid(x: torch.Tensor, y: torch.Tensor, NT: int, *, C1: float = C_DEFAULT,
             stream=None) -> list:
     """Multi-scale IQA matrices: tiles of NT, 2NT, 4NT, ... up to the largest
     power-of-two multiple of NT that divides N (the whole image when N/NT is a
-    power of two).  One fused pass over the images, then a chain of merges."""
+    power of two).  One fused pass over the images, then all merges of 2 x 2
+    tiles in one launch per six levels."""
+    if D is None:
+        D = default_D(C1)
     levels = [iqa_tiles(x, y, NT, C1=C1, C2=C2, C=C, D=D, sums=True, stream=stream)]
     ns = x.shape[0] // NT
-    while ns % 2 == 0:
-        levels.append(merge_tiles(levels[-1].sums, 2, C1=C1, C2=C2, C=C, D=D, stream=stream))
-        ns //= 2
+    n = ns
+    dev = x.device
+    while n % 2 == 0:
+        n //= 2
+        levels.append(TileResult(torch.empty((n, n), dtype=torch.float32, device=dev),
+                                 torch.empty((n, n), dtype=torch.float32, device=dev),
+                                 torch.empty((n * n, 4), dtype=torch.float32, device=dev)))
+    if len(levels) == 1:
+        return levels
+    count = len(levels) - 1
+    ptrs = [(ctypes.c_void_p * count)(*[t[k].data_ptr() for t in levels[1:]]) for k in range(3)]
+    with torch.cuda.device(dev):
+        st = _lib.load().iqa_pyramid(levels[0].sums.data_ptr(), ns, count, D, C2, C, *ptrs,
+                                     _stream_handle(dev, stream))
+    _lib.check(st, "iqa_pyramid")
+    _mark_used(stream, *(t for lv in levels[1:] for t in lv))
     return levels
