@@ -17,7 +17,8 @@ import torch
 
 from . import _lib
 from ._lib import IqaPair, LaunchCfg
-from .iqa import C_DEFAULT, TileResult, _check_images, _mark_used, _stream_handle, default_D
+from .iqa import (C_DEFAULT, TileResult, _check_images, _mark_used, _on_device, _stream_handle,
+                  default_D, iqa_tiles)
 
 
 def default_waves() -> int:
@@ -117,29 +118,28 @@ class Batch:
         N_T % 4 == 0 and 16-byte aligned images (descriptors in the kernel
         arguments or in a device table), and a single-pair launch for each of
         the others, all on the same stream."""
-        from .iqa import iqa_tiles
-        with torch.cuda.device(self.device):
-            if self.descs_host is not None:
-                st = _lib.load().iqa_tiles_batched_inline(self.descs_host.ctypes.data, self.count,
-                                                          self.units, self.waves,
-                                                          _stream_handle(self.device, stream))
-                _lib.check(st, "iqa_tiles_batched_inline")
-            elif self.descs is not None:
-                st = _lib.load().iqa_tiles_batched(self.descs.data_ptr(), self.count, self.units,
-                                                   self.waves,
-                                                   _stream_handle(self.device, stream))
-                _lib.check(st, "iqa_tiles_batched")
-            for i in self.single:
-                x, y, NT = self.inputs[i]
-                r = self.results[i]
-                out = {"lisi": r.lisi, "auglisi": r.auglisi}
-                if r.sums is not None:
-                    out["sums"] = r.sums
-                iqa_tiles(x, y, NT, sums=r.sums is not None, out=out, stream=stream,
-                          **self.consts)
-            # the outputs and the descriptor table were allocated on torch's
-            # current stream; the launches may run on another torch stream
-            _mark_used(stream, self.descs, self.out)
+        _on_device(self.device, self._launch, stream)
+
+    def _launch(self, stream) -> None:
+        if self.descs_host is not None:
+            st = _lib.load().iqa_tiles_batched_inline(self.descs_host.ctypes.data, self.count,
+                                                      self.units, self.waves,
+                                                      _stream_handle(self.device, stream))
+            _lib.check(st, "iqa_tiles_batched_inline")
+        elif self.descs is not None:
+            st = _lib.load().iqa_tiles_batched(self.descs.data_ptr(), self.count, self.units,
+                                               self.waves, _stream_handle(self.device, stream))
+            _lib.check(st, "iqa_tiles_batched")
+        for i in self.single:
+            x, y, NT = self.inputs[i]
+            r = self.results[i]
+            out = {"lisi": r.lisi, "auglisi": r.auglisi}
+            if r.sums is not None:
+                out["sums"] = r.sums
+            iqa_tiles(x, y, NT, sums=r.sums is not None, out=out, stream=stream, **self.consts)
+        # the outputs and the descriptor table were allocated on torch's
+        # current stream; the launches may run on another torch stream
+        _mark_used(stream, self.descs, self.out)
 
     def capture(self, stream: Optional[torch.cuda.Stream] = None) -> torch.cuda.CUDAGraph:
         """Capture one run into a HIP graph; replay it with ``graph.replay()``
