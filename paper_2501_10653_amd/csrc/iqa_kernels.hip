@@ -254,6 +254,7 @@ template <> struct VecT<1> { using T = float; };
 // checks the LDS aperture and counts on both wait counters.  ANY: a quad at any
 // float address (the hardware takes a 16-byte global load at 4-byte alignment).
 #define IQA_GLOBAL __attribute__((address_space(1)))
+#define IQA_CONSTANT __attribute__((address_space(4)))
 
 template <int VEC, bool ANY = false>
 __device__ __forceinline__ typename VecT<VEC>::T vload(const IQA_GLOBAL char *p) {
@@ -378,7 +379,7 @@ __device__ __forceinline__ void finalize(const PairArgs &a, int64_t t, const Sum
 // gets one contiguous range of logical workgroups keeps every XCD streaming
 // from all column offsets (and so from all of its L2 channels) instead of the
 // one offset class that b % 8 would give it.
-constexpr int kXcds = 8;
+constexpr int kLogXcds = 3, kXcds = 1 << kLogXcds;
 
 __device__ __forceinline__ int xcd_remap(uint32_t b, uint32_t grid) {
     const uint32_t xcd = b % kXcds;
@@ -946,7 +947,10 @@ __host__ __device__ __forceinline__ int64_t batch_units(const PairArgs &a) {
 // lines and DRAM pages, on one XCD: 128 units where there are enough (four
 // 4096^2/128 pairs, 4096 units: chunks of 128 units 86.8 us, 64 90.0, 16 91.6),
 // else a 32nd of all units, at most 32 (512 pairs of 256^2/32, 2048 units:
-// 46.2 with 32, 48.6 with 64).
+// 44.3 with 32, 46.6 with 64).  The units left over after the last whole round
+// of chunks are divided evenly: dealt as chunks, some XCDs had up to a chunk
+// more than others (22 ragged pairs, 6690 units: 139 us against 132; 29
+// pairs of 256^2/32: 7.4 against 6.9).
 __host__ __device__ __forceinline__ int unit_chunk_log(int64_t units) {
     if (units >= 4096) return 7;
     int r = 0;
@@ -960,14 +964,18 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int log_chunk = unit_chunk_log(units);
-    const uint32_t xcds = gridDim.x < kXcds ? gridDim.x : kXcds;
-    const uint32_t xcd = blockIdx.x % xcds;
-    const uint32_t stride = gridDim.x / xcds + (xcd < gridDim.x % xcds ? 1 : 0);
-    for (int64_t i = blockIdx.x / xcds;; i += stride) {
-        const int64_t first = ((i >> log_chunk) * xcds + xcd) << log_chunk;
-        if (first >= units) break;
-        const int64_t u = first + (i & ((1 << log_chunk) - 1));
-        if (u >= units) continue;
+    // Fewer workgroups than XCDs are dealt to as if there were one.
+    const int log_xcds = gridDim.x < kXcds ? 0 : kLogXcds;
+    const uint32_t xcds = 1u << log_xcds, xcd = blockIdx.x & (xcds - 1);
+    const uint32_t stride = (gridDim.x - xcd + xcds - 1) >> log_xcds;
+    // The XCD's units: `whole` in chunks, then its share of what is left over.
+    const int64_t whole = units >> (log_chunk + log_xcds) << log_chunk;
+    const int64_t share = (units - (whole << log_xcds) + xcds - 1) >> log_xcds;
+    for (int64_t i = blockIdx.x >> log_xcds; i < whole + share; i += stride) {
+        const int64_t u = i < whole ? ((((i >> log_chunk) << log_xcds) + xcd) << log_chunk) +
+                                          (i & ((1 << log_chunk) - 1))
+                                    : (whole << log_xcds) + xcd * share + (i - whole);
+        if (u >= units) break;
         // Binary search for the pair whose units contain u (same in every wave).
         int lo = 0, hi = count - 1;
         while (lo < hi) {
@@ -1031,7 +1039,9 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
 template <int U>
 __global__ __launch_bounds__(kBatchWaves * kWave, 3) void batch_kernel(const BatchDesc *descs,
                                                                        int count, int64_t units) {
-    batch_body<U>(descs, count, units);
+    // No kernel writes the table while one reads it: constant memory, so that
+    // a unit's descriptor is read into scalar registers.
+    batch_body<U>((const BatchDesc *)(const IQA_CONSTANT BatchDesc *)(uintptr_t)descs, count, units);
 }
 
 // Up to CAP descriptors passed by value in the kernel arguments: no table to
@@ -2027,12 +2037,10 @@ iqa_status check_outputs_params(float *lisi, float *auglisi, float *sums, float 
 }
 
 // Workgroups of a batch launch: as many as `waves` gives, but no more than one
-// per unit of each XCD's share.
+// per unit of the XCD with the most.
 int64_t batch_grid(int64_t waves, int64_t units) {
-    const int log_chunk = unit_chunk_log(units);
-    const int64_t chunks = (units + (int64_t(1) << log_chunk) - 1) >> log_chunk;
-    const int64_t all = ((chunks + kXcds - 1) / kXcds * kXcds) << log_chunk;
-    return std::min(waves / kBatchWaves, chunks < kXcds ? units : all);
+    const int64_t all = (units + kXcds - 1) / kXcds * kXcds;
+    return std::min(waves / kBatchWaves, units < kXcds ? units : all);
 }
 
 template <int CAP>
