@@ -356,6 +356,16 @@ iqa_status iqa_tiles_batched(const void *descs_dev, int64_t count, int64_t total
 iqa_status iqa_tiles_batched_inline(const void *descs_host, int64_t count,
                                     int64_t total_units, int64_t waves, void *stream);
 
+/* The pairs a batch cannot take, in one launch of their own: iqa_batch_describe
+ * and iqa_tiles_batched for pairs with NT >= 4 and either NT % 4 != 0 or images
+ * off a 16-byte boundary, whose default launch is not split (else
+ * IQA_ERR_CONFIG).  One workgroup per unit, which is one of iqa_tiles'
+ * workgroups; results are bitwise iqa_tiles'. */
+iqa_status iqa_odd_batch_describe(const iqa_pair *pairs, int64_t count, void *descs,
+                                  int64_t *total_units);
+iqa_status iqa_odd_tiles_batched(const void *descs_dev, int64_t count, int64_t total_units,
+                                 void *stream);
+
 /* ------------------------------------------------------------------------ */
 /* Serving: continuous batching of snapshot-vs-reference requests            */
 /* ------------------------------------------------------------------------ */

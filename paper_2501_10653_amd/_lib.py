@@ -159,6 +159,9 @@ def load() -> ctypes.CDLL:
         "iqa_batch_describe": ([ctypes.POINTER(IqaPair), i64, vp, ctypes.POINTER(i64)],
                                ctypes.c_int),
         "iqa_tiles_batched": ([vp, i64, i64, i64, vp], ctypes.c_int),
+        "iqa_odd_batch_describe": ([ctypes.POINTER(IqaPair), i64, vp, ctypes.POINTER(i64)],
+                                   ctypes.c_int),
+        "iqa_odd_tiles_batched": ([vp, i64, i64, vp], ctypes.c_int),
         "iqa_tiles_batched_inline": ([vp, i64, i64, i64, vp], ctypes.c_int),
         "iqa_server_create": ([ctypes.POINTER(ServerOpts), ctypes.POINTER(vp)], ctypes.c_int),
         "iqa_server_create_dry": ([ctypes.POINTER(ServerOpts), i64, ctypes.c_double,

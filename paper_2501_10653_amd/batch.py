@@ -40,9 +40,10 @@ class Batch:
 
     ``pairs`` is a sequence of ``(x, y, NT)`` with x, y contiguous float32
     N x N device tensors.  Pairs with NT % 4 == 0 and 16-byte aligned images go
-    into the persistent launch; any others are launched one by one on the same
-    stream.  Output tensors are allocated here and reused by every run:
-    ``results[i]`` is the :class:`TileResult` of pair i.
+    into the persistent launch; the others share a launch that does what a
+    launch of iqa_tiles each would, or are launched one by one (tiles split over
+    workgroups, N_T < 4), on the same stream.  Output tensors are allocated here
+    and reused by every run: ``results[i]`` is the :class:`TileResult` of pair i.
     """
 
     def __init__(self, pairs: Sequence, *, C1: float = C_DEFAULT, C2: float = C_DEFAULT,
@@ -95,29 +96,47 @@ class Batch:
         self.inline = (self.count <= _lib.BATCH_INLINE_MAX) if inline is None else bool(inline)
         if self.inline and self.count > _lib.BATCH_INLINE_MAX:
             raise ValueError(f"inline batches hold at most {_lib.BATCH_INLINE_MAX} pairs")
+        lib = _lib.load()
         if batched:
-            arr = (IqaPair * len(batched))()
-            for k, i in enumerate(batched):
-                x, y, NT = self.inputs[i]
-                r = self.results[i]
-                arr[k] = IqaPair(x.data_ptr(), y.data_ptr(), x.shape[0], NT, D, C1, C2, C,
-                                 r.lisi.data_ptr(), r.auglisi.data_ptr(),
-                                 r.sums.data_ptr() if r.sums is not None else None)
-            host = np.zeros(len(batched) * _lib.BATCH_DESC_BYTES, np.uint8)
-            units = ctypes.c_int64(0)
-            _lib.check(_lib.load().iqa_batch_describe(arr, len(batched), host.ctypes.data,
-                                                      ctypes.byref(units)), "iqa_batch_describe")
-            self.units = int(units.value)
+            st, host, self.units = self._describe(lib.iqa_batch_describe, batched)
+            _lib.check(st, "iqa_batch_describe")
             if self.inline:
                 self.descs_host = host
             else:
                 self.descs = torch.from_numpy(host).to(self.device)   # device copy, 256-B aligned
+        # What iqa_odd_batch_describe refuses, iqa_tiles launches (or refuses).
+        odd = [i for i in self.single if self.inputs[i][0].device == self.out.device and
+               self._describe(lib.iqa_odd_batch_describe, [i])[0] == 0]
+        self.odd_count, self.odd_units, self.odd_descs = 0, 0, None
+        if len(odd) > 1:
+            st, host, units = self._describe(lib.iqa_odd_batch_describe, odd)
+            if st == 0:
+                self.odd_count, self.odd_units = len(odd), units
+                self.odd_descs = torch.from_numpy(host).to(self.device)
+        taken = set(odd) if self.odd_descs is not None else ()
+        self.alone = [i for i in self.single if i not in taken]
+
+    def _describe(self, describe, which):
+        """Status, descriptors (host) and units of the pairs ``which``."""
+        c = self.consts
+        arr = (IqaPair * len(which))()
+        for k, i in enumerate(which):
+            x, y, NT = self.inputs[i]
+            r = self.results[i]
+            arr[k] = IqaPair(x.data_ptr(), y.data_ptr(), x.shape[0], NT, c["D"], c["C1"], c["C2"],
+                             c["C"], r.lisi.data_ptr(), r.auglisi.data_ptr(),
+                             r.sums.data_ptr() if r.sums is not None else None)
+        host = np.zeros(len(which) * _lib.BATCH_DESC_BYTES, np.uint8)
+        units = ctypes.c_int64(0)
+        st = describe(arr, len(which), host.ctypes.data, ctypes.byref(units))
+        return st, host, int(units.value)
 
     def run(self, stream=None) -> None:
         """Enqueue the batch: one persistent launch over every pair with
         N_T % 4 == 0 and 16-byte aligned images (descriptors in the kernel
-        arguments or in a device table), and a single-pair launch for each of
-        the others, all on the same stream."""
+        arguments or in a device table), one for the others that share a
+        launch, and a single-pair launch for each of the rest, all on the same
+        stream."""
         _on_device(self.device, self._launch, stream)
 
     def _launch(self, stream) -> None:
@@ -130,7 +149,11 @@ class Batch:
             st = _lib.load().iqa_tiles_batched(self.descs.data_ptr(), self.count, self.units,
                                                self.waves, _stream_handle(self.device, stream))
             _lib.check(st, "iqa_tiles_batched")
-        for i in self.single:
+        if self.odd_descs is not None:
+            _lib.check(_lib.load().iqa_odd_tiles_batched(
+                self.odd_descs.data_ptr(), self.odd_count, self.odd_units,
+                _stream_handle(self.device, stream)), "iqa_odd_tiles_batched")
+        for i in self.alone:
             x, y, NT = self.inputs[i]
             r = self.results[i]
             out = {"lisi": r.lisi, "auglisi": r.auglisi}
@@ -139,7 +162,7 @@ class Batch:
             iqa_tiles(x, y, NT, sums=r.sums is not None, out=out, stream=stream, **self.consts)
         # the outputs and the descriptor table were allocated on torch's
         # current stream; the launches may run on another torch stream
-        _mark_used(stream, self.descs, self.out)
+        _mark_used(stream, self.descs, self.odd_descs, self.out)
 
     def capture(self, stream: Optional[torch.cuda.Stream] = None) -> torch.cuda.CUDAGraph:
         """Capture one run into a HIP graph; replay it with ``graph.replay()``

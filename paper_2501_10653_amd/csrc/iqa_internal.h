@@ -8,7 +8,9 @@
 namespace iqa {
 
 // iqa_batch_describe with the per-pair geometry of tuned kind `kind`
-// (IQA_TUNE_BATCH: the ragged-batch geometry; IQA_TUNE_SERVE: the server's).
+// (IQA_TUNE_BATCH: the ragged-batch geometry; IQA_TUNE_SERVE: the server's;
+// kDescribeOdd: iqa_odd_batch_describe).
+constexpr int kDescribeOdd = -1;
 iqa_status describe_pairs(const iqa_pair *pairs, int64_t count, void *descs,
                           int64_t *total_units, int kind);
 

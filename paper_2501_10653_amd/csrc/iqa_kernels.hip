@@ -958,7 +958,7 @@ __host__ __device__ __forceinline__ int unit_chunk_log(int64_t units) {
     return r;
 }
 
-template <int U>
+template <int U, bool ODD = false>
 __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, int64_t units) {
     __shared__ float4 lds[kBatchWaves][kWave];
     const int lane = threadIdx.x & (kWave - 1);
@@ -987,9 +987,9 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
         // A unit outside the pair's units (a unit count or pair count that
         // does not match the table) is skipped, never read.
         const int64_t g64 = u - descs[pi].unit_begin;
-        if (g64 < 0 || g64 >= batch_units(a)) continue;
+        if (g64 < 0 || g64 >= (ODD ? (int64_t)a.ns * a.ngx : batch_units(a))) continue;
         const bool leader = (lane & ((1 << a.log_grp) - 1)) == 0;
-        if (!batch_coop(a)) {
+        if (!ODD && !batch_coop(a)) {
             const int64_t grp64 = g64 * kBatchWaves + wave;
             if (grp64 >= (int64_t)a.ns * a.ngx) continue;
             const int grp = (int)grp64;
@@ -1004,8 +1004,8 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
             const int grp = (int)g64;
             const int ty = udiv(grp, a.ngx_m, a.ngx);
             const int txg = grp - ty * a.ngx;
-            const Sum4 s = batch_wrap(a) ? slice_sums<4, false, U, kBoth, true>(a, ty, txg, wave, lane)
-                                     : slice_sums<4, false, U, kBoth, false>(a, ty, txg, wave, lane);
+            const Sum4 s = batch_wrap(a) ? slice_sums<4, ODD, U, kBoth, true>(a, ty, txg, wave, lane)
+                                     : slice_sums<4, ODD, U, kBoth, false>(a, ty, txg, wave, lane);
             if (leader) lds[wave][lane >> a.log_grp] = float4{s.A, s.P, s.X, s.Y};
             __syncthreads();
             // Two waves finish the tiles at once, as in the tile kernel.
@@ -1042,6 +1042,20 @@ __global__ __launch_bounds__(kBatchWaves * kWave, 3) void batch_kernel(const Bat
     // No kernel writes the table while one reads it: constant memory, so that
     // a unit's descriptor is read into scalar registers.
     batch_body<U>((const BatchDesc *)(const IQA_CONSTANT BatchDesc *)(uintptr_t)descs, count, units);
+}
+
+// The pairs whose quads lie at any address (N_T % 4 != 0, images off 16 bytes):
+// a unit is one of the tile kernel's workgroups, four waves on the quarters of a
+// group's rows, so the results are bitwise a single launch's.  Launched one by
+// one, small odd pairs are bound by their launches: 21 pairs of 240^2 to 2140^2,
+// 9 of them odd, 0.22 GB (32 us of reads), took 69 us a run and take 48.
+constexpr int kOddUnroll = 4;
+static_assert(kAnyWaves == kBatchWaves, "an odd unit is a workgroup of the tile kernel");
+
+__global__ __launch_bounds__(kBatchWaves * kWave) void odd_batch_kernel(const BatchDesc *descs,
+                                                                        int count, int64_t units) {
+    batch_body<kOddUnroll, true>(
+        (const BatchDesc *)(const IQA_CONSTANT BatchDesc *)(uintptr_t)descs, count, units);
 }
 
 // Up to CAP descriptors passed by value in the kernel arguments: no table to
@@ -2209,6 +2223,11 @@ iqa_status iqa_batch_describe(const iqa_pair *pairs, int64_t count, void *descs,
     return iqa::describe_pairs(pairs, count, descs, total_units, IQA_TUNE_BATCH);
 }
 
+iqa_status iqa_odd_batch_describe(const iqa_pair *pairs, int64_t count, void *descs,
+                                  int64_t *total_units) {
+    return iqa::describe_pairs(pairs, count, descs, total_units, iqa::kDescribeOdd);
+}
+
 }  // extern "C"
 
 iqa_status iqa::describe_pairs(const iqa_pair *pairs, int64_t count, void *descs,
@@ -2223,12 +2242,17 @@ iqa_status iqa::describe_pairs(const iqa_pair *pairs, int64_t count, void *descs
         if (st != IQA_OK) return st;
         st = check_outputs_params(p.lisi, p.auglisi, p.sums, p.D, p.C1, p.C2, p.C);
         if (st != IQA_OK) return st;
-        if (p.NT % 4 != 0) return IQA_ERR_CONFIG;
-        if (!aligned(p.x, 16) || !aligned(p.y, 16)) return IQA_ERR_ALIGN;
-        const iqa_launch_cfg c = kind == IQA_TUNE_SERVE ? serve_cfg(p.N, p.NT) : batch_cfg(p.N, p.NT);
+        const bool odd = kind == kDescribeOdd;
+        if (!odd && p.NT % 4 != 0) return IQA_ERR_CONFIG;
+        const uintptr_t unit = odd ? 4 : 16;
+        if (!aligned(p.x, unit) || !aligned(p.y, unit)) return IQA_ERR_ALIGN;
+        const iqa_launch_cfg c = odd                      ? pick_cfg(p.N, p.NT, p.x, p.y)
+                                 : kind == IQA_TUNE_SERVE ? serve_cfg(p.N, p.NT)
+                                                          : batch_cfg(p.N, p.NT);
         Geometry g{};
         st = geometry(p.N, p.NT, c, g);
         if (st != IQA_OK) return st;
+        if (odd && (!g.any || c.ksplit != 1)) return IQA_ERR_CONFIG;
         BatchDesc d;
         std::memset(&d, 0, sizeof(d));
         // Outputs a pair does not ask for stay NULL; the batch always computes
@@ -2237,7 +2261,7 @@ iqa_status iqa::describe_pairs(const iqa_pair *pairs, int64_t count, void *descs
                   p.lisi || p.sums ? p.C1 : 1.f, p.lisi || p.sums ? p.C2 : 1.f,
                   p.auglisi || p.sums ? p.C : 1.f, p.lisi, p.auglisi, p.sums, c, g);
         d.unit_begin = units;
-        units += batch_units(d.a);
+        units += odd ? g.groups : batch_units(d.a);
         std::memcpy(out + i, &d, sizeof(d));
     }
     if (units > ((int64_t)1 << 40)) return IQA_ERR_SHAPE;
@@ -2257,6 +2281,18 @@ iqa_status iqa_tiles_batched(const void *descs_dev, int64_t count, int64_t total
     const int64_t blocks = batch_grid(waves, total_units);
     return hip_status(launch_kernel(&batch_kernel<kBatchUnroll>, (unsigned)blocks,
                                     kBatchWaves * kWave, static_cast<hipStream_t>(stream),
+                                    static_cast<const BatchDesc *>(descs_dev), (int)count,
+                                    total_units));
+}
+
+iqa_status iqa_odd_tiles_batched(const void *descs_dev, int64_t count, int64_t total_units,
+                                 void *stream) {
+    if (!descs_dev) return IQA_ERR_NULL;
+    if (count < 1 || count > INT_MAX || total_units < 1) return IQA_ERR_SHAPE;
+    if (!aligned(descs_dev, 16)) return IQA_ERR_ALIGN;
+    const int64_t blocks = batch_grid((int64_t)INT_MAX / kXcds * kXcds * kBatchWaves, total_units);
+    return hip_status(launch_kernel(&odd_batch_kernel, (unsigned)blocks, kBatchWaves * kWave,
+                                    static_cast<hipStream_t>(stream),
                                     static_cast<const BatchDesc *>(descs_dev), (int)count,
                                     total_units));
 }

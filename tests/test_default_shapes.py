@@ -8,7 +8,7 @@ import ctypes
 import random
 
 from paper_2501_10653_amd import _lib
-from paper_2501_10653_amd._lib import LaunchCfg
+from paper_2501_10653_amd._lib import IqaPair, LaunchCfg
 
 
 def test_default_shapes_are_accepted_and_bounded():
@@ -32,3 +32,34 @@ def test_default_shapes_are_accepted_and_bounded():
             assert c.ksplit * c.waves * 16 <= 64 << 10
             assert c.seg * c.rp == 64 and c.waves in (1, 2, 4, 8, 16)
     assert split > 100
+
+
+def test_odd_batches_take_what_a_single_launch_of_any_address_quads_takes():
+    """iqa_odd_batch_describe accepts exactly the pairs whose default shape is
+    unsplit quads at any address, with one unit per workgroup of that launch."""
+    lib = _lib.load()
+    rng = random.Random(12)
+    c, units = LaunchCfg(), ctypes.c_int64()
+    desc = ctypes.create_string_buffer(_lib.BATCH_DESC_BYTES)
+    taken = 0
+    for _ in range(4000):
+        NT = int(2 ** rng.uniform(0, 9))
+        N = NT * max(1, int(2 ** rng.uniform(0, 7)))
+        x, y = (256 + 4 * rng.choice((0, 0, 1, 2, 3)) for _ in range(2))
+        pair = IqaPair(x, y, N, NT, 5e-7, 1e-6, 1e-6, 1e-6, 4096, 8192, None)
+        st = lib.iqa_odd_batch_describe(ctypes.byref(pair), 1, desc, ctypes.byref(units))
+        assert lib.iqa_default_cfg(N, NT, x, y, ctypes.byref(c)) == 0
+        if c.vec < 4 and NT >= 4 and c.ksplit == 1:
+            taken += 1
+            assert st == 0
+            assert units.value == lib.iqa_launch_workgroups(N, NT, ctypes.byref(c))
+        else:
+            assert _lib.STATUS_NAMES[st] == "IQA_ERR_CONFIG"
+    assert 1000 < taken < 3500
+    pair.x = 257
+    st = lib.iqa_odd_batch_describe(ctypes.byref(pair), 1, desc, ctypes.byref(units))
+    assert _lib.STATUS_NAMES[st] == "IQA_ERR_ALIGN"
+    assert lib.iqa_odd_tiles_batched(None, 1, 1, None) == 1
+    assert lib.iqa_odd_tiles_batched(4096, 0, 1, None) == 2
+    assert lib.iqa_odd_tiles_batched(4096, 1, 0, None) == 2
+    assert lib.iqa_odd_tiles_batched(4104, 1, 1, None) == 3
