@@ -375,8 +375,8 @@ iqa_status iqa_odd_tiles_batched(const void *descs_dev, int64_t count, int64_t t
  * scheduler thread admits requests in arrival order while the bytes held by
  * admitted, unfinished requests stay within `hbm_budget_bytes` (a request
  * holds its snapshot, 4*N*N bytes, plus its output matrices), and packs all
- * admitted requests into one batched launch (iqa_tiles_batched_inline up to
- * IQA_BATCH_INLINE_MAX requests, else iqa_tiles_batched) whenever one of
+ * admitted requests into one batched launch (the descriptors of up to 31
+ * requests in its arguments, else in a table copied first) whenever one of
  * `streams` launch slots is free.  After each batch the slot's stream runs a
  * one-thread kernel that stores the batch's number into a word of pinned host
  * memory; the slot frees when the scheduler sees that word change (no HIP

@@ -1060,8 +1060,8 @@ __global__ __launch_bounds__(kBatchWaves * kWave) void odd_batch_kernel(const Ba
 
 // Up to CAP descriptors passed by value in the kernel arguments: no table to
 // copy to the device before the launch.  The waves read the descriptors
-// straight from the kernel-argument segment.  Instantiated for CAP = 1, 4 and
-// IQA_BATCH_INLINE_MAX: a launch uses the smallest that holds its batch,
+// straight from the kernel-argument segment.  Instantiated for CAP = 1, 4,
+// IQA_BATCH_INLINE_MAX and kArgsMax: a launch uses the smallest that holds its batch,
 // because the host-side cost of a launch grows with its argument size.
 template <int CAP>
 struct InlineDescs {
@@ -2300,7 +2300,15 @@ iqa_status iqa_odd_tiles_batched(const void *descs_dev, int64_t count, int64_t t
 iqa_status iqa_tiles_batched_inline(const void *descs_host, int64_t count, int64_t total_units,
                                     int64_t waves, void *stream) {
     if (!descs_host) return IQA_ERR_NULL;
-    if (count < 1 || count > IQA_BATCH_INLINE_MAX || total_units < 1) return IQA_ERR_SHAPE;
+    if (count > IQA_BATCH_INLINE_MAX) return IQA_ERR_SHAPE;
+    return iqa::tiles_batched_args(descs_host, count, total_units, waves, stream);
+}
+
+}  // extern "C"
+
+iqa_status iqa::tiles_batched_args(const void *descs_host, int64_t count, int64_t total_units,
+                                   int64_t waves, void *stream) {
+    if (count < 1 || count > kArgsMax || total_units < 1) return IQA_ERR_SHAPE;
     if (waves < kBatchWaves || waves % kBatchWaves != 0 || waves / kBatchWaves > INT_MAX)
         return IQA_ERR_CONFIG;
     // The table is on the host here, so its unit numbering is checked: pair i
@@ -2317,7 +2325,9 @@ iqa_status iqa_tiles_batched_inline(const void *descs_host, int64_t count, int64
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (count == 1) return launch_inline<1>(descs_host, count, total_units, blocks, s);
     if (count <= 4) return launch_inline<4>(descs_host, count, total_units, blocks, s);
-    return launch_inline<IQA_BATCH_INLINE_MAX>(descs_host, count, total_units, blocks, s);
+    if (count <= IQA_BATCH_INLINE_MAX)
+        return launch_inline<IQA_BATCH_INLINE_MAX>(descs_host, count, total_units, blocks, s);
+    return launch_inline<kArgsMax>(descs_host, count, total_units, blocks, s);
 }
 
 iqa_status iqa_merge_tiles(const float *sums_in, int64_t ns, int64_t f, float D, float C2,

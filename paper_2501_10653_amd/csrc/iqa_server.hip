@@ -103,12 +103,12 @@ constexpr int64_t kErrorCheckNs = 1000000;
 // that shows as a burst of millisecond latencies at the start of a server's
 // life.  At creation the server therefore runs every launch form it can use
 // once, on a tiny zero pair, and waits for it: the batch kernel with 1, 4 and
-// IQA_BATCH_INLINE_MAX descriptors in its arguments and with a descriptor
+// IQA_BATCH_INLINE_MAX and kArgsMax descriptors in its arguments and with a descriptor
 // table (as far as max_batch allows), and the publishing kernel on every slot
 // stream (storing 0, the word's initial value).  Returns the first HIP error.
 hipError_t warm_up(std::vector<Slot> &slots, const iqa_server_opts &o) {
     constexpr int64_t kN = 32;   // one 32 x 32 tile per pair
-    constexpr int64_t kPairs = IQA_BATCH_INLINE_MAX + 1;
+    constexpr int64_t kPairs = iqa::kArgsMax + 1;
     const int64_t img = kN * kN;
     float *buf = nullptr;
     hipError_t e = hipMalloc(reinterpret_cast<void **>(&buf),
@@ -116,7 +116,7 @@ hipError_t warm_up(std::vector<Slot> &slots, const iqa_server_opts &o) {
     if (e != hipSuccess) return e;
     Slot &s0 = slots[0];
     e = hipMemsetAsync(buf, 0, (size_t)img * sizeof(float), s0.stream);
-    const int64_t counts[] = {1, 4, IQA_BATCH_INLINE_MAX, IQA_BATCH_INLINE_MAX + 1};
+    const int64_t counts[] = {1, 4, IQA_BATCH_INLINE_MAX, iqa::kArgsMax, iqa::kArgsMax + 1};
     int64_t prev = 0;
     for (int64_t c : counts) {
         c = std::min<int64_t>(c, o.max_batch);
@@ -131,8 +131,8 @@ hipError_t warm_up(std::vector<Slot> &slots, const iqa_server_opts &o) {
         if (iqa::describe_pairs(pairs.data(), c, s0.desc_host, &units, IQA_TUNE_SERVE) != IQA_OK)
             break;
         iqa_status st;
-        if (c <= IQA_BATCH_INLINE_MAX) {
-            st = iqa_tiles_batched_inline(s0.desc_host, c, units, o.waves, s0.stream);
+        if (c <= iqa::kArgsMax) {
+            st = iqa::tiles_batched_args(s0.desc_host, c, units, o.waves, s0.stream);
         } else {
             e = hipMemcpyAsync(s0.desc_dev, s0.desc_host, (size_t)c * IQA_BATCH_DESC_BYTES,
                                hipMemcpyHostToDevice, s0.stream);
@@ -259,8 +259,9 @@ bool iqa_server::launch(Slot &s, std::vector<Pending> &batch) {
                                   IQA_TUNE_SERVE) != IQA_OK)
         ok = false;
     // Small batches carry their descriptors in the kernel arguments (one
-    // enqueue); larger ones copy the table to the slot's device buffer first.
-    const bool inl = pairs.size() <= (size_t)IQA_BATCH_INLINE_MAX;
+    // enqueue); larger ones copy the table to the slot's device buffer first
+    // (24 requests, 1.5 GB, from submit to poll: 4 us more of 275).
+    const bool inl = pairs.size() <= (size_t)iqa::kArgsMax;
     if (ok && !inl) {
         hipError_t e = hipMemcpyAsync(s.desc_dev, s.desc_host,
                                       pairs.size() * IQA_BATCH_DESC_BYTES,
@@ -272,7 +273,7 @@ bool iqa_server::launch(Slot &s, std::vector<Pending> &batch) {
     }
     if (ok) {
         const iqa_status st =
-            inl ? iqa_tiles_batched_inline(s.desc_host, (int64_t)pairs.size(), units, opts.waves,
+            inl ? iqa::tiles_batched_args(s.desc_host, (int64_t)pairs.size(), units, opts.waves,
                                            s.stream)
                 : iqa_tiles_batched(s.desc_dev, (int64_t)pairs.size(), units, opts.waves,
                                     s.stream);
