@@ -913,7 +913,7 @@ __global__ __launch_bounds__(kWave) void combine_kernel(KArgs a) {
 //   * a pair whose geometry has kBatchWaves waves per tile group gives each
 //     tile group a unit of its own: the waves take its row slices and combine
 //     them in LDS exactly as tiles_kernel does.
-// A grid smaller than the units is persistent (see unit_chunk_log).  Either way
+// A grid smaller than the units is persistent (see kLogChunk).  Either way
 // a pair's results are bitwise equal to a single-pair launch with the same
 // geometry and unroll (ksplit 1).
 struct BatchDesc {
@@ -938,42 +938,34 @@ __host__ __device__ __forceinline__ int64_t batch_units(const PairArgs &a) {
     return batch_coop(a) ? groups : (groups + kBatchWaves - 1) / kBatchWaves;
 }
 
-// How units are dealt to the XCDs: chunks of 2^unit_chunk_log consecutive units
-// go to the eight of them in turn, so that each gets its share of every pair,
-// and an XCD's workgroups take its units in turn.  (One contiguous range of
-// workgroups per XCD, as in the tile kernel, gave the second round of units to
-// one XCD: 30 ragged pairs, 1.2 GB, 245 us against 184; and units of unequal
-// cost, 203 against 180.)  Chunks keep neighbouring tile groups, which share
-// lines and DRAM pages, on one XCD: 128 units where there are enough (four
-// 4096^2/128 pairs, 4096 units: chunks of 128 units 86.8 us, 64 90.0, 16 91.6),
-// else a 32nd of all units, at most 32 (512 pairs of 256^2/32, 2048 units:
-// 44.3 with 32, 46.6 with 64).  The units left over after the last whole round
-// of chunks are divided evenly: dealt as chunks, some XCDs had up to a chunk
-// more than others (22 ragged pairs, 6690 units: 139 us against 132; 29
-// pairs of 256^2/32: 7.4 against 6.9).
-__host__ __device__ __forceinline__ int unit_chunk_log(int64_t units) {
-    if (units >= 4096) return 7;
-    int r = 0;
-    while (r < 5 && (int64_t(64) << r) <= units) ++r;
-    return r;
-}
+// How units are dealt to the XCDs: chunks of 2^kLogChunk consecutive units go
+// to the eight of them in turn, so that each gets its share of every pair, what
+// is left after the last whole round is divided evenly, and an XCD's workgroups
+// take its units in turn.  (One contiguous range of workgroups per XCD, as in
+// the tile kernel, gave the second round of units to one XCD: 30 ragged pairs,
+// 1.2 GB, 245 us against 177; units of unequal cost 203 against 180; the rest
+// dealt as chunks: 22 ragged pairs 139 against 132.)  Chunks keep neighbouring
+// tile groups, which share lines and DRAM pages, on one XCD: 128 units, or
+// all of an XCD's where there are fewer (one 4096^2/128 pair, 1024 units: 24.2
+// us, with chunks of 64 26.8, 32 27.1, 8 30.1, 1 33.5; four: 86.5, 64 90.0, 16
+// 91.6; 512 pairs of 256^2/32, which share nothing: 45.6, 32 43.9).
+constexpr int kLogChunk = 7;
 
 template <int U, bool ODD = false>
 __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, int64_t units) {
     __shared__ float4 lds[kBatchWaves][kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int log_chunk = unit_chunk_log(units);
     // Fewer workgroups than XCDs are dealt to as if there were one.
     const int log_xcds = gridDim.x < kXcds ? 0 : kLogXcds;
     const uint32_t xcds = 1u << log_xcds, xcd = blockIdx.x & (xcds - 1);
     const uint32_t stride = (gridDim.x - xcd + xcds - 1) >> log_xcds;
     // The XCD's units: `whole` in chunks, then its share of what is left over.
-    const int64_t whole = units >> (log_chunk + log_xcds) << log_chunk;
+    const int64_t whole = units >> (kLogChunk + log_xcds) << kLogChunk;
     const int64_t share = (units - (whole << log_xcds) + xcds - 1) >> log_xcds;
     for (int64_t i = blockIdx.x >> log_xcds; i < whole + share; i += stride) {
-        const int64_t u = i < whole ? ((((i >> log_chunk) << log_xcds) + xcd) << log_chunk) +
-                                          (i & ((1 << log_chunk) - 1))
+        const int64_t u = i < whole ? ((((i >> kLogChunk) << log_xcds) + xcd) << kLogChunk) +
+                                          (i & ((1 << kLogChunk) - 1))
                                     : (whole << log_xcds) + xcd * share + (i - whole);
         if (u >= units) break;
         // Binary search for the pair whose units contain u (same in every wave).
@@ -2329,6 +2321,8 @@ iqa_status iqa::tiles_batched_args(const void *descs_host, int64_t count, int64_
         return launch_inline<IQA_BATCH_INLINE_MAX>(descs_host, count, total_units, blocks, s);
     return launch_inline<kArgsMax>(descs_host, count, total_units, blocks, s);
 }
+
+extern "C" {
 
 iqa_status iqa_merge_tiles(const float *sums_in, int64_t ns, int64_t f, float D, float C2,
                            float C, float *lisi, float *auglisi, float *sums_out, void *stream) {
