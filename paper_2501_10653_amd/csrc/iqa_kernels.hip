@@ -1025,9 +1025,9 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
 }
 
 // The descriptor table in device memory (any number of pairs).  Bound by HBM: 30
-// ragged pairs (1.2 GB) run at 6.6 TB/s, 256 at 6.8, a plain read at 6.9.  Three
+// ragged pairs (1.2 GB) run at 6.7 TB/s, 256 at 6.9, a plain read at 6.9.  Three
 // waves per SIMD: more waves with fewer loads each in flight are slower on mixed
-// batches (loads in batches of four, five waves: 223 us against 184 for the 30).
+// batches (loads in batches of four, five waves: 223 us for the 30, 184 with eight).
 template <int U>
 __global__ __launch_bounds__(kBatchWaves * kWave, 3) void batch_kernel(const BatchDesc *descs,
                                                                        int count, int64_t units) {
