@@ -1522,6 +1522,14 @@ iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g)
 // quads: 6 items 8.5, 12 items 9.7), and two rows at 32 lanes (8190^2/90: 85.8
 // and 88.2).
 //
+// Eight waves per workgroup instead of four, unsplit, where there is a workgroup
+// for more than half of the CUs and at most one for each, from 16 items per lane
+// (of four) to 64 (of eight).  (1920^2/160, 144 workgroups: 8.9 us, split four
+// ways 10.7, unsplit 11.4; 2800^2/200, 196: 13.0, 14.4, 14.8; 3072^2/256, 144:
+// 16.0, 17.7, 18.0; 3200^2/200, 256: 15.7, four waves 16.6; but 1920^2/120, 15
+// items, 256: 8.0 and 7.8; 2880^2/160, 324: 16.3 and 14.9; 3520^2/320, 121: 22.1,
+// split in two 20.0; 4800^2/400, 78 items of eight, 144: 36.2, split 33.4.)
+//
 // Splits.  A tile whose waves would each make more than 24 items is split over
 // workgroups if the launch has less than one of four waves per CU: into the fewest parts that give it that, as long as a lane keeps 3
 // items.  (Unsplit against split: 1000^2/100, 13 items, 5.7 and 6.2;
@@ -1561,6 +1569,12 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     c.seg = (int)std::min<int64_t>(lanes, next_pow2(NT / c.vec));
     c.rp = (int)(lanes / c.seg);
     const int64_t tiles = ns * ns;
+    const bool most_cus = workgroups() > 128 && workgroups() <= 256;
+    if (c.vec == 4 && NT % 8 == 0 && lanes == kWave && most_cus && items(rows) >= 16 &&
+        items(NT / 8) <= 64) {
+        c.waves = 8;
+        return c;
+    }
     if (workgroups() * wg_waves >= 1024 || items(rows) <= 24 || lanes < kWave) return c;
     if (c.vec == 4 && tiles <= 16 && NT % 8 == 0) c.waves = 8, wg_waves = 8;
     auto enough = [&](int64_t wgs) { return wgs >= 225 && (wgs <= 256 || wgs >= 448); };

@@ -34,6 +34,16 @@ def test_default_shapes_are_accepted_and_bounded():
     assert split > 100
 
 
+def test_eight_waves_for_a_workgroup_on_most_cus():
+    lib = _lib.load()
+    c = LaunchCfg()
+    for ns, NT, eight in [(11, 160, False), (12, 160, True), (16, 160, True), (17, 160, False),
+                          (12, 120, False), (12, 128, True), (12, 320, True), (12, 400, False),
+                          (12, 164, False)]:
+        assert lib.iqa_default_cfg(ns * NT, NT, 256, 256, ctypes.byref(c)) == 0
+        assert (c.waves == 8 and c.ksplit == 1) == eight, (ns, NT, c.as_dict())
+
+
 def test_odd_batches_take_what_a_single_launch_of_any_address_quads_takes():
     """iqa_odd_batch_describe accepts exactly the pairs whose default shape is
     unsplit quads at any address, with one unit per workgroup of that launch."""
