@@ -163,7 +163,7 @@ def candidates_batch(NT: int) -> List[dict]:
 
 
 def tune_batch(NTs: Sequence[int] = (32, 64, 128), Ns: Sequence[int] = (512, 1024, 2048, 4096),
-               copies: int = 8, waves_list: Sequence[int] = (1024, 2048, 4096, 8192, 16384),
+               copies: int = 8, waves_list: Sequence[int] = (1024, 2048, 4096, 8192, 16384, 262144),
                log=None) -> Tuple[Dict[int, dict], int, list]:
     """Per-N_T batch geometry and the persistent wave count, timed on a batch
     of `copies` pairs of every (N, N_T)."""
