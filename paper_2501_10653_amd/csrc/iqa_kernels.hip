@@ -1527,8 +1527,14 @@ iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g)
 // (of four) to 64 (of eight).  (1920^2/160, 144 workgroups: 8.9 us, split four
 // ways 10.7, unsplit 11.4; 2800^2/200, 196: 13.0, 14.4, 14.8; 3072^2/256, 144:
 // 16.0, 17.7, 18.0; 3200^2/200, 256: 15.7, four waves 16.6; but 1920^2/120, 15
-// items, 256: 8.0 and 7.8; 2880^2/160, 324: 16.3 and 14.9; 3520^2/320, 121: 22.1,
-// split in two 20.0; 4800^2/400, 78 items of eight, 144: 36.2, split 33.4.)
+// items, 256: 8.0 and 7.8; 2880^2/160, 324: 16.3 and 14.9; 4800^2/400, 78 items
+// of eight, 144: 36.2, split 33.4.)  For a few less, which would be split in only
+// two, up to 24 items of eight (121 workgroups: 1760^2/160 8.6 and 9.1, 2112^2/192
+// 10.2 and 10.6; 2200^2/200 11.3 and 11.2, 3520^2/320 22.1 and 20.0; 100 of them,
+// split in five: 1600^2/160 8.5 and 8.1).  Tiles too small to be split, from
+// 14 items per lane (of four), take sixteen waves on up to 200 workgroups
+// (1152^2/128, 81: 5.7, four waves 6.4; 1792^2/128, 196: 6.9 and 7.5; 1120^2/112:
+// 5.6 and 6.1; 2048^2/128, 256, eight waves 7.9, sixteen 8.1).
 //
 // Splits.  A tile whose waves would each make more than 24 items is split over
 // workgroups if the launch has less than one of four waves per CU: into the fewest parts that give it that, as long as a lane keeps 3
@@ -1569,11 +1575,12 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     c.seg = (int)std::min<int64_t>(lanes, next_pow2(NT / c.vec));
     c.rp = (int)(lanes / c.seg);
     const int64_t tiles = ns * ns;
-    const bool most_cus = workgroups() > 128 && workgroups() <= 256;
-    if (c.vec == 4 && NT % 8 == 0 && lanes == kWave && most_cus && items(rows) >= 16 &&
-        items(NT / 8) <= 64) {
-        c.waves = 8;
-        return c;
+    if (c.vec == 4 && lanes == kWave && workgroups() <= 256) {
+        const int64_t wgs = workgroups(), each = items(rows);
+        if (NT % 16 == 0 && each >= 14 && each <= 24 && wgs <= 200) c.waves = 16;
+        else if (NT % 8 == 0 && each >= 16 && wgs > 112 && items(NT / 8) <= (wgs > 128 ? 64 : 24))
+            c.waves = 8;
+        if (c.waves > 4) return c;
     }
     if (workgroups() * wg_waves >= 1024 || items(rows) <= 24 || lanes < kWave) return c;
     if (c.vec == 4 && tiles <= 16 && NT % 8 == 0) c.waves = 8, wg_waves = 8;

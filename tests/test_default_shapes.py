@@ -37,11 +37,15 @@ def test_default_shapes_are_accepted_and_bounded():
 def test_eight_waves_for_a_workgroup_on_most_cus():
     lib = _lib.load()
     c = LaunchCfg()
-    for ns, NT, eight in [(11, 160, False), (12, 160, True), (16, 160, True), (17, 160, False),
-                          (12, 120, False), (12, 128, True), (12, 320, True), (12, 400, False),
+    for ns, NT, eight in [(10, 160, False), (11, 160, True), (11, 200, False), (12, 160, True), (16, 160, True), (17, 160, False),
+                          (12, 120, False), (15, 128, True), (12, 320, True), (12, 400, False),
                           (12, 164, False)]:
         assert lib.iqa_default_cfg(ns * NT, NT, 256, 256, ctypes.byref(c)) == 0
         assert (c.waves == 8 and c.ksplit == 1) == eight, (ns, NT, c.as_dict())
+    for ns, NT, sixteen in [(1, 128, True), (14, 128, True), (15, 128, False), (2, 120, False),
+                            (8, 112, True), (8, 96, False), (3, 160, False)]:
+        assert lib.iqa_default_cfg(ns * NT, NT, 256, 256, ctypes.byref(c)) == 0
+        assert (c.waves == 16 and c.ksplit == 1) == sixteen, (ns, NT, c.as_dict())
 
 
 def test_odd_batches_take_what_a_single_launch_of_any_address_quads_takes():

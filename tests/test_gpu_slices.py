@@ -37,7 +37,7 @@ def place(img, off):
 DEFAULTS = [(4, 4), (8, 4), (10, 5), (14, 7), (18, 6), (63, 9), (122, 61), (128, 64), (130, 65),
             (253, 253), (510, 255), (257, 257), (514, 257), (516, 258), (300, 300), (600, 300),
             (750, 250), (450, 225), (520, 260), (1018, 509),
-            (1536, 128), (1920, 160), (2560, 160), (2720, 160)]
+            (128, 128), (384, 128), (1408, 128), (1536, 128), (1760, 160), (1920, 160), (2560, 160), (2720, 160)]
 
 
 @pytest.mark.parametrize("off", [0, 1, 2])
