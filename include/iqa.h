@@ -43,7 +43,9 @@
  *   decides),
  *   allocated and cleared on first use and reused afterwards (an outgrown
  *   buffer is kept until the process ends, so graphs captured earlier stay
- *   valid).  The first call for a given (device, stream, shape) must
+ *   valid).  hipStreamPerThread is a stream of its own in every host thread,
+ *   with a workspace of its own; a thread that used one waits for that stream
+ *   when it ends.  The first call for a given (device, stream, shape) must
  *   therefore not happen while the stream is being captured into a graph:
  *   call iqa_prepare() (or the entry point itself) once before.
  *   Default launches of tile sides that powers of two do not divide far

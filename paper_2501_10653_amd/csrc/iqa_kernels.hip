@@ -1715,8 +1715,8 @@ iqa_launch_cfg serve_cfg(int64_t N, int64_t NT) {
 // counters only) followed by a partial-sum region.  A launch uses its
 // workspace from its first workgroup to its last, and launches on one stream
 // run one after the other, so one buffer per stream is enough; concurrent
-// streams get their own.  A new buffer is cleared on its stream before first
-// use, and since each launch leaves its counters at zero, the counter region
+// streams get their own (hipStreamPerThread: one per host thread).  A new
+// buffer is cleared on its stream before first use, and since each launch leaves its counters at zero, the counter region
 // stays all zeros between launches whatever shapes share it.  A buffer that
 // is outgrown is kept, not freed: a graph captured earlier may still launch
 // kernels that use it.
@@ -1726,8 +1726,49 @@ struct Workspace {
     size_t part_bytes = 0;   // partial-sum region, at ptr + cnt_bytes
 };
 std::mutex g_ws_mutex;
-std::map<std::tuple<int, void *, bool>, Workspace> g_ws;
+std::map<std::tuple<int, void *, int, bool>, Workspace> g_ws;
 std::vector<void *> g_ws_retired;
+
+// hipStreamPerThread is one handle for a stream of every host thread, so its
+// buffers are a thread's too.  Threads that use it are numbered; a thread that
+// ends waits for its streams and hands its number, and so its buffers, on.
+std::mutex g_thread_mutex;
+std::vector<bool> g_thread_used;   // by number, from 0
+
+class ThreadNumber {
+public:
+    // Of this thread, which uses its stream of device `dev`.
+    int on(int dev) {
+        if (number_ < 0) {
+            std::lock_guard<std::mutex> lock(g_thread_mutex);
+            number_ = (int)(std::find(g_thread_used.begin(), g_thread_used.end(), false) -
+                            g_thread_used.begin());
+            if (number_ == (int)g_thread_used.size()) g_thread_used.push_back(false);
+            g_thread_used[number_] = true;
+        }
+        if (std::find(devices_.begin(), devices_.end(), dev) == devices_.end())
+            devices_.push_back(dev);
+        return number_;
+    }
+    ~ThreadNumber() {
+        if (number_ < 0) return;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // leave others' captures alone
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        for (int dev : devices_) {
+            // A stream that cannot be waited for keeps the number.
+            if (hipSetDevice(dev) != hipSuccess ||
+                hipStreamSynchronize(hipStreamPerThread) != hipSuccess)
+                return;
+        }
+        std::lock_guard<std::mutex> lock(g_thread_mutex);
+        g_thread_used[number_] = false;
+    }
+
+private:
+    int number_ = -1;
+    std::vector<int> devices_;
+};
+thread_local ThreadNumber t_thread;
 
 // Split launches of at most this many workgroups (one round on gfx950's 256
 // CUs at four workgroups each) add their parts by ticket, within the launch;
@@ -1769,7 +1810,8 @@ iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float *
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_status(e);
-    Workspace &w = g_ws[{dev, (void *)s, own}];
+    const int thread = s == hipStreamPerThread ? t_thread.on(dev) : -1;
+    Workspace &w = g_ws[{dev, (void *)s, thread, own}];
     if (w.cnt_bytes < need.cnt_bytes || w.part_bytes < need.part_bytes) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (s != nullptr) {

@@ -1,0 +1,119 @@
+/* Host-side rules of the launches, without a GPU: this program defines the HIP
+ * calls that the library makes (its own definitions go before the runtime's),
+ * hands out host memory for device memory, records what would be launched, and
+ * refuses launches that HIP refuses.  Nothing runs and nothing reads an image.
+ *
+ *   c_fake_device SCENARIO    exit status 0: as expected; prints what was not
+ */
+#include <pthread.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "iqa.h"
+
+typedef struct { uint32_t x, y, z; } dim3_t;
+
+static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
+static int mallocs, launches, captured_mallocs;
+static size_t malloc_bytes;
+static void *capturing;          /* the stream that is being captured */
+static uint64_t last_items;      /* work items of the last launch */
+static size_t last_lds;
+static char scratch[1 << 20];
+
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipSetDevice(int d) { (void)d; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipMalloc(void **p, size_t n) {
+    pthread_mutex_lock(&mu);
+    ++mallocs;
+    captured_mallocs += capturing != NULL;
+    malloc_bytes += n;
+    pthread_mutex_unlock(&mu);
+    *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+    return *p ? 0 : 2;
+}
+int hipFree(void *p) { free(p); return 0; }
+int hipMemsetAsync(void *p, int v, size_t n, void *s) { (void)s; memset(p, v, n); return 0; }
+int hipStreamIsCapturing(void *s, int *st) { *st = s == capturing ? 1 : 0; return 0; }
+int hipThreadExchangeStreamCaptureMode(int *m) { (void)m; return 0; }
+int hipStreamSynchronize(void *s) { (void)s; return 0; }
+int hipGetSymbolAddress(void **p, const void *sym) { (void)sym; *p = scratch; return 0; }
+int hipLaunchKernel(const void *fn, dim3_t grid, dim3_t block, void **args, size_t lds, void *s) {
+    (void)fn, (void)args, (void)s;
+    const uint64_t items = (uint64_t)grid.x * block.x;
+    pthread_mutex_lock(&mu);
+    ++launches;
+    last_items = items;
+    last_lds = lds;
+    pthread_mutex_unlock(&mu);
+    return items >> 32 ? 9 : 0;   /* hipErrorInvalidConfiguration */
+}
+
+#define CHECK(c) do { if (!(c)) { printf("%s:%d: %s\n", __FILE__, __LINE__, #c); return 1; } } while (0)
+
+static const float *const X = (const float *)(uintptr_t)(1 << 20), *const Y = (const float *)(uintptr_t)(2 << 20);
+static float *const OUT = (float *)(uintptr_t)(3 << 20), *const OUT2 = (float *)(uintptr_t)(4 << 20);
+static void *const PER_THREAD = (void *)(uintptr_t)2;   /* hipStreamPerThread */
+
+static int tiles_at(const float *x, int64_t N, int64_t NT, const iqa_launch_cfg *c, void *s) {
+    return iqa_tiles_cfg(x, Y, N, NT, 5e-7f, 1e-6f, 1e-6f, 1e-6f, OUT, OUT2, NULL, c, s);
+}
+
+static int tiles(int64_t N, int64_t NT, void *s) { return tiles_at(X, N, NT, NULL, s); }
+
+static int merge(void *s) {
+    return iqa_merge_tiles(X, 512, 512, 5e-7f, 1e-6f, 1e-6f, OUT, OUT2, NULL, s);
+}
+
+/* ---- hipStreamPerThread is a stream of its own in each host thread ---- */
+
+typedef struct { int which, status, mallocs; } Job;
+
+static int split_call(int which) {
+    switch (which) {
+        case 0: return merge(PER_THREAD);
+        case 1: return tiles(3000, 300, PER_THREAD);   /* split by the built-in rule alone */
+        default: return tiles(2048, 256, PER_THREAD);  /* split by the tuned table */
+    }
+}
+
+static void *thread_main(void *p) {
+    Job *j = p;
+    const int before = mallocs;
+    j->status = split_call(j->which);
+    if (j->status == 0) j->status = split_call(j->which);
+    j->mallocs = mallocs - before;
+    return NULL;
+}
+
+static int per_thread(void) {
+    for (int which = 0; which < 3; ++which) {
+        const int start = mallocs;
+        Job mine = {which, 0, 0}, other = {which, 0, 0};
+        thread_main(&mine);
+        pthread_t t;
+        CHECK(pthread_create(&t, NULL, thread_main, &other) == 0);
+        pthread_join(t, NULL);
+        CHECK(mine.status == 0 && other.status == 0);
+        if (which != 1) CHECK(mine.mallocs == 1);      /* 0 and 1 use the same buffer */
+        if (which != 1) CHECK(other.mallocs == 1);     /* not the first thread's */
+        /* Threads that come and go pass their buffers on. */
+        for (int i = 0; i < 20; ++i) {
+            CHECK(pthread_create(&t, NULL, thread_main, &other) == 0);
+            pthread_join(t, NULL);
+            CHECK(other.status == 0);
+        }
+        CHECK(mallocs - start <= 2);
+    }
+    return 0;
+}
+
+int main(int argc, char **argv) {
+    const char *name = argc > 1 ? argv[1] : "";
+    if (!strcmp(name, "per_thread")) return per_thread();
+    printf("no scenario %s\n", name);
+    return 2;
+}

@@ -1,0 +1,39 @@
+"""The host side of the launches without a GPU: which buffers and launches a
+call takes, on the CPU, through a C program that stands in for the HIP runtime
+(tests/c_fake_device.c)."""
+
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2501_10653_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+pytestmark = pytest.mark.skipif(not shutil.which("gcc"), reason="needs gcc")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    _lib.load()
+    exe = str(tmp_path_factory.mktemp("fake") / "c_fake_device")
+    pkg = os.path.dirname(_lib.LIB_PATH)
+    subprocess.run(["gcc", "-O1", "-Wall", "-Werror", "-rdynamic", "-pthread", "-I",
+                    os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "c_fake_device.c"),
+                    "-o", exe, "-L", pkg, "-liqa_hip", f"-Wl,-rpath,{pkg}",
+                    "-Wl,--allow-shlib-undefined"], check=True)
+    return exe
+
+
+def scenario(program, name):
+    res = subprocess.run([program, name], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_per_thread_streams_share_no_workspace(program):
+    """hipStreamPerThread is one handle for a stream of every host thread."""
+    scenario(program, "per_thread")
