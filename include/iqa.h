@@ -40,7 +40,7 @@
  *   The two give the same bits.  Those launches use a small library-owned
  *   device workspace per (device, stream) (16 bytes per tile and split part,
  *   at least 128 per part and 128 more per tile group where a ticket counter
- *   decides),
+ *   decides; 192 KiB or more in all),
  *   allocated and cleared on first use and reused afterwards (an outgrown
  *   buffer is kept until the process ends, so graphs captured earlier stay
  *   valid).  hipStreamPerThread is a stream of its own in every host thread,
@@ -51,7 +51,8 @@
  *   Default launches of tile sides that powers of two do not divide far
  *   enough (say 300 or 225) split too, but carry none of these rules: captured,
  *   or through iqa_tiles_noalloc, they run without any workspace, bitwise the
- *   same, and slower (one workgroup per tile).
+ *   same, and slower (one workgroup per tile); so they do on any stream beyond
+ *   the first 128 that took a workspace for them.
  * Threads.  Every entry point may be called from several host threads at
  *   once, on the same stream or on different ones.  Calls on one stream run
  *   in the order they were enqueued, each launch finishing before the next

@@ -1803,15 +1803,30 @@ bool capturing(hipStream_t s) {
     return hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
 }
 
+// Least sizes of a workspace's regions: what any launch with ticket counters
+// needs, so that a buffer rarely grows.
+constexpr size_t kCounterBytes = 64 << 10, kPartBytes = 128 << 10;
+
+// The launches that can do without a workspace (run and merge) keep buffers for
+// this many streams at most, of at most two sizes each; on further streams they
+// do without.
+constexpr int kMostOwn = 128;
+int g_own_buffers = 0;
+
 // *part receives the partial-sum region; the counter region ends where it
-// starts.  `own`: the buffer of the default launches that never use a
-// workspace under capture.  The caller holds g_ws_mutex.
+// starts.  `own`: a buffer of the launches that can do without.  The caller
+// holds g_ws_mutex.
 iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float **part) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_status(e);
     const int thread = s == hipStreamPerThread ? t_thread.on(dev) : -1;
-    Workspace &w = g_ws[{dev, (void *)s, thread, own}];
+    const auto key = std::make_tuple(dev, (void *)s, thread, own);
+    if (own && g_own_buffers >= kMostOwn) {
+        const auto it = g_ws.find(key);
+        if (it == g_ws.end() || !it->second.ptr) return IQA_ERR_SCRATCH;
+    }
+    Workspace &w = g_ws[key];
     if (w.cnt_bytes < need.cnt_bytes || w.part_bytes < need.part_bytes) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (s != nullptr) {
@@ -1819,8 +1834,9 @@ iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float *
             if (e != hipSuccess) return hip_status(e);
         }
         if (cs != hipStreamCaptureStatusNone) return IQA_ERR_CAPTURE;
-        const size_t cb = round_up(std::max(need.cnt_bytes, w.cnt_bytes), 4096);
-        const size_t pb = round_up(std::max(need.part_bytes, w.part_bytes), 4096);
+        const size_t cb = round_up(std::max({need.cnt_bytes, w.cnt_bytes, kCounterBytes}), 4096);
+        size_t pb = round_up(std::max({need.part_bytes, w.part_bytes, kPartBytes}), 4096);
+        if (own && pb > kPartBytes) pb = std::max(pb, (size_t)IQA_NOALLOC_SCRATCH_BYTES);
         void *p = nullptr;
         // A launch that needs no preparation may come while another stream is
         // being captured: the allocation must not disturb that.
@@ -1835,12 +1851,23 @@ iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float *
             return hip_status(e);
         }
         if (w.ptr) g_ws_retired.push_back(w.ptr);
+        else if (own) ++g_own_buffers;
         w.ptr = p;
         w.cnt_bytes = cb;
         w.part_bytes = pb;
     }
     *part = reinterpret_cast<float *>(static_cast<char *>(w.ptr) + w.cnt_bytes);
     return IQA_OK;
+}
+
+// Whether a launch that can do without has a workspace.  The caller holds
+// g_ws_mutex.
+bool own_workspace(hipStream_t s, const SplitNeed &need, float **part) {
+    const int err = g_last_hip_error;
+    if (workspace_for(s, true, need, part) == IQA_OK) return true;
+    (void)hipGetLastError();
+    g_last_hip_error = err;
+    return false;
 }
 
 // Scratch of the no-allocation entry point: a fixed array in device memory,
@@ -2007,10 +2034,10 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
             a.ws = reinterpret_cast<float *>(reinterpret_cast<char *>(base) + kScratchCounterBytes);
         } else {
             ws_lock.lock();
-            st = workspace_for(s, own, need, &a.ws);
-            if (st != IQA_OK && !own) return st;
-            if (st != IQA_OK) {   // no memory to be had: do without
-                (void)hipGetLastError();
+            if (!own) {
+                st = workspace_for(s, false, need, &a.ws);
+                if (st != IQA_OK) return st;
+            } else if (!own_workspace(s, need, &a.ws)) {
                 ws_lock.unlock();
                 local = true;
             }
@@ -2073,11 +2100,8 @@ iqa_status merge(const float *sums_in, int64_t ns, int64_t f, float D, float C2,
         need.cnt_bytes = (size_t)(parents * kLine);
         need.part_bytes = (size_t)(parents * m.parts * kLine);
         lock.lock();
-        if (workspace_for(s, true, need, &m.ws) != IQA_OK) {
-            (void)hipGetLastError();
-            lock.unlock();
-            local = true;
-        }
+        local = !own_workspace(s, need, &m.ws);
+        if (local) lock.unlock();
     }
     if (local)
         return hip_status(launch_with_lds(&merge_local_kernel, (unsigned)parents,

@@ -111,9 +111,27 @@ static int per_thread(void) {
     return 0;
 }
 
+/* ---- streams that come and go: the buffers that no caller asked for end ---- */
+
+static int many_streams(void) {
+    for (uintptr_t s = 1 << 12; s < 600 << 12; s += 1 << 12) {
+        CHECK(merge((void *)s) == 0);
+        CHECK(tiles(3000, 300, (void *)s) == 0);
+    }
+    CHECK(mallocs <= 128);
+    CHECK(malloc_bytes <= 64 << 20);
+    CHECK(last_lds > 0);                    /* without a workspace: in LDS */
+    const int before = mallocs;
+    CHECK(merge((void *)(uintptr_t)(1 << 12)) == 0 && last_lds == 0);   /* the first keeps its own */
+    CHECK(tiles(2048, 256, (void *)(uintptr_t)(700 << 12)) == 0);       /* a prepared split always has one */
+    CHECK(mallocs == before + 1 && iqa_last_hip_error() == 0);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "per_thread")) return per_thread();
+    if (!strcmp(name, "many_streams")) return many_streams();
     printf("no scenario %s\n", name);
     return 2;
 }

@@ -37,3 +37,8 @@ def scenario(program, name):
 def test_per_thread_streams_share_no_workspace(program):
     """hipStreamPerThread is one handle for a stream of every host thread."""
     scenario(program, "per_thread")
+
+
+def test_buffers_that_no_caller_asked_for_are_bounded(program):
+    """Merges and default splits without a prepare rule, on ever new streams."""
+    scenario(program, "many_streams")
