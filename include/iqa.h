@@ -210,8 +210,9 @@ iqa_status iqa_tiles_noalloc(const float *x, const float *y, int64_t N, int64_t 
                              const iqa_launch_cfg *cfg, void *stream);
 
 /* Allocate, ahead of time, the workspace that (N, NT) with `cfg` (NULL =
- * default) needs on `stream`, so that later calls allocate nothing (e.g.
- * under graph capture).  IQA_OK when nothing or everything was allocated. */
+ * default, for images of any alignment) needs on `stream`, so that later calls
+ * allocate nothing (e.g. under graph capture).  IQA_OK when nothing or
+ * everything was allocated. */
 iqa_status iqa_prepare(int64_t N, int64_t NT, const iqa_launch_cfg *cfg, void *stream);
 
 /* ------------------------------------------------------------------------ */

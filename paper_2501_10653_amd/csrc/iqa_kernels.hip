@@ -2248,9 +2248,15 @@ iqa_status iqa_check_cfg(int64_t N, int64_t NT, const iqa_launch_cfg *cfg) {
 iqa_status iqa_prepare(int64_t N, int64_t NT, const iqa_launch_cfg *cfg, void *stream) {
     iqa_status st = check_shape(N, NT);
     if (st != IQA_OK) return st;
-    const float *probe = reinterpret_cast<const float *>(uintptr_t(256));
-    return run(probe, probe, N, NT, 1.f, 1.f, 1.f, 1.f, nullptr, nullptr, nullptr, cfg, stream,
-               Ws::kPrepare);
+    // The default shape, and so its parts, depends on how the images are
+    // aligned: what it needs at 16, 8 and 4 bytes.
+    for (uintptr_t at : {256, 264, 260}) {
+        const float *probe = reinterpret_cast<const float *>(at);
+        st = run(probe, probe, N, NT, 1.f, 1.f, 1.f, 1.f, nullptr, nullptr, nullptr, cfg, stream,
+                 Ws::kPrepare);
+        if (st != IQA_OK || cfg) return st;
+    }
+    return IQA_OK;
 }
 
 iqa_status iqa_tune_set(int64_t N, int64_t NT, int kind, const iqa_launch_cfg *cfg) {

@@ -1,6 +1,6 @@
 /* Host-side rules of the launches, without a GPU: this program defines the HIP
  * calls that the library makes (its own definitions go before the runtime's),
- * hands out host memory for device memory, records what would be launched, and
+ * hands out addresses for device memory, records what would be launched, and
  * refuses launches that HIP refuses.  Nothing runs and nothing reads an image.
  *
  *   c_fake_device SCENARIO    exit status 0: as expected; prints what was not
@@ -18,6 +18,7 @@ typedef struct { uint32_t x, y, z; } dim3_t;
 static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static int mallocs, launches, captured_mallocs;
 static size_t malloc_bytes;
+static uintptr_t next_address = (uintptr_t)1 << 40;   /* of device memory that does not exist */
 static void *capturing;          /* the stream that is being captured */
 static uint64_t last_items;      /* work items of the last launch */
 static size_t last_lds;
@@ -31,12 +32,13 @@ int hipMalloc(void **p, size_t n) {
     ++mallocs;
     captured_mallocs += capturing != NULL;
     malloc_bytes += n;
+    *p = (void *)next_address;
+    next_address += (n + 4095) / 4096 * 4096;
     pthread_mutex_unlock(&mu);
-    *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
-    return *p ? 0 : 2;
+    return 0;
 }
-int hipFree(void *p) { free(p); return 0; }
-int hipMemsetAsync(void *p, int v, size_t n, void *s) { (void)s; memset(p, v, n); return 0; }
+int hipFree(void *p) { (void)p; return 0; }
+int hipMemsetAsync(void *p, int v, size_t n, void *s) { (void)p, (void)v, (void)n, (void)s; return 0; }
 int hipStreamIsCapturing(void *s, int *st) { *st = s == capturing ? 1 : 0; return 0; }
 int hipThreadExchangeStreamCaptureMode(int *m) { (void)m; return 0; }
 int hipStreamSynchronize(void *s) { (void)s; return 0; }
@@ -128,10 +130,34 @@ static int many_streams(void) {
     return 0;
 }
 
+/* ---- iqa_prepare stands for the shape, wherever its images lie ---- */
+
+static int prepared(void) {
+    int refused = 0;
+    uintptr_t stream = 1 << 12;
+    for (int64_t NT = 4; NT <= 4096; ++NT) {
+        for (int64_t ns = 1; ns <= 32 && ns * NT <= 16384; ++ns, stream += 1 << 12) {
+            void *s = (void *)stream;
+            CHECK(iqa_prepare(ns * NT, NT, NULL, s) == 0);
+            capturing = s;
+            for (int off = 0; off < 4; ++off) {
+                const int st = tiles_at(X + off, ns * NT, NT, NULL, s);
+                if (st != 0 && refused++ < 5)
+                    printf("%d/%d off %d: %s\n", (int)(ns * NT), (int)NT, off, iqa_status_str(st));
+            }
+            capturing = NULL;
+        }
+    }
+    printf("%d refused\n", refused);
+    CHECK(captured_mallocs == 0 && refused == 0);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "per_thread")) return per_thread();
     if (!strcmp(name, "many_streams")) return many_streams();
+    if (!strcmp(name, "prepared")) return prepared();
     printf("no scenario %s\n", name);
     return 2;
 }

@@ -42,3 +42,8 @@ def test_per_thread_streams_share_no_workspace(program):
 def test_buffers_that_no_caller_asked_for_are_bounded(program):
     """Merges and default splits without a prepare rule, on ever new streams."""
     scenario(program, "many_streams")
+
+
+def test_prepare_covers_images_at_any_address(program):
+    """iqa_prepare(N, NT), then the capture of images off a 16-byte boundary."""
+    scenario(program, "prepared")
