@@ -1574,6 +1574,11 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     }
     c.seg = (int)std::min<int64_t>(lanes, next_pow2(NT / c.vec));
     c.rp = (int)(lanes / c.seg);
+    // HIP launches fewer than 2^32 work items (131072^2/4: one wave).
+    if (c.vec == 4 && workgroups() * wg_waves * kWave > (int64_t)UINT32_MAX) {
+        c.waves = 1;
+        return c;
+    }
     const int64_t tiles = ns * ns;
     if (c.vec == 4 && lanes == kWave && workgroups() <= 256) {
         const int64_t wgs = workgroups(), each = items(rows);

@@ -153,11 +153,27 @@ static int prepared(void) {
     return 0;
 }
 
+/* ---- every size the library documents can be launched ---- */
+
+static int sizes(void) {
+    /* 2^17 pixels a side in the smallest tiles that were ever launched */
+    CHECK(tiles(1 << 17, 4, NULL) == 0);
+    for (int64_t NT = 6; NT <= 64; ++NT) {
+        const int64_t N = (1 << 17) / NT * NT;
+        if (NT != 7 && tiles(N, NT, NULL) != 0) {
+            printf("%d/%d refused\n", (int)N, (int)NT);
+            return 1;
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "per_thread")) return per_thread();
     if (!strcmp(name, "many_streams")) return many_streams();
     if (!strcmp(name, "prepared")) return prepared();
+    if (!strcmp(name, "sizes")) return sizes();
     printf("no scenario %s\n", name);
     return 2;
 }

@@ -47,3 +47,9 @@ def test_buffers_that_no_caller_asked_for_are_bounded(program):
 def test_prepare_covers_images_at_any_address(program):
     """iqa_prepare(N, NT), then the capture of images off a 16-byte boundary."""
     scenario(program, "prepared")
+
+
+def test_the_largest_images_can_be_launched(program):
+    """HIP launches fewer than 2^32 work items; 2^17 pixels a side with tiles of
+    4 pixels are 2^30 tiles."""
+    scenario(program, "sizes")
