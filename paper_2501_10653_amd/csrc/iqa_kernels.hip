@@ -2135,10 +2135,13 @@ iqa_status check_outputs_params(float *lisi, float *auglisi, float *sums, float 
 }
 
 // Workgroups of a batch launch: as many as `waves` gives, but no more than one
-// per unit of the XCD with the most.
+// per unit of the XCD with the most, and than HIP launches (fewer than 2^32 work
+// items); they share what is left.
+constexpr int64_t kMostBlocks = UINT32_MAX / (kBatchWaves * kWave) / kXcds * kXcds;
+
 int64_t batch_grid(int64_t waves, int64_t units) {
     const int64_t all = (units + kXcds - 1) / kXcds * kXcds;
-    return std::min(waves / kBatchWaves, units < kXcds ? units : all);
+    return std::min({waves / kBatchWaves, units < kXcds ? units : all, kMostBlocks});
 }
 
 template <int CAP>
@@ -2380,7 +2383,7 @@ iqa_status iqa_odd_tiles_batched(const void *descs_dev, int64_t count, int64_t t
     if (!descs_dev) return IQA_ERR_NULL;
     if (count < 1 || count > INT_MAX || total_units < 1) return IQA_ERR_SHAPE;
     if (!aligned(descs_dev, 16)) return IQA_ERR_ALIGN;
-    const int64_t blocks = batch_grid((int64_t)INT_MAX / kXcds * kXcds * kBatchWaves, total_units);
+    const int64_t blocks = batch_grid(kMostBlocks * kBatchWaves, total_units);
     return hip_status(launch_kernel(&odd_batch_kernel, (unsigned)blocks, kBatchWaves * kWave,
                                     static_cast<hipStream_t>(stream),
                                     static_cast<const BatchDesc *>(descs_dev), (int)count,

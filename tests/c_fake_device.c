@@ -168,12 +168,25 @@ static int sizes(void) {
     return 0;
 }
 
+/* ---- batches of any number of units ---- */
+
+static int many_units(void) {
+    const int64_t units[] = {1, 7, 8, 9, 1 << 20, (1 << 24) - 1, 1 << 24, (1 << 24) + 9, (int64_t)1 << 40};
+    for (unsigned i = 0; i < sizeof units / sizeof *units; ++i) {
+        CHECK(iqa_odd_tiles_batched(X, 1, units[i], NULL) == 0);
+        CHECK(units[i] > 1 << 23 || last_items / 256 == (units[i] < 8 ? units[i] : (units[i] + 7) / 8 * 8));
+        CHECK(iqa_tiles_batched(X, 1, units[i], (int64_t)1 << 32, NULL) == 0);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "per_thread")) return per_thread();
     if (!strcmp(name, "many_streams")) return many_streams();
     if (!strcmp(name, "prepared")) return prepared();
     if (!strcmp(name, "sizes")) return sizes();
+    if (!strcmp(name, "many_units")) return many_units();
     printf("no scenario %s\n", name);
     return 2;
 }

@@ -53,3 +53,8 @@ def test_the_largest_images_can_be_launched(program):
     """HIP launches fewer than 2^32 work items; 2^17 pixels a side with tiles of
     4 pixels are 2^30 tiles."""
     scenario(program, "sizes")
+
+
+def test_batches_of_any_number_of_units_can_be_launched(program):
+    """The batch kernels are persistent: their grid is capped, not refused."""
+    scenario(program, "many_units")
