@@ -52,7 +52,9 @@
  *   enough (say 300 or 225) split too, but carry none of these rules: captured,
  *   or through iqa_tiles_noalloc, they run without any workspace, bitwise the
  *   same, and slower (one workgroup per tile); so they do on any stream beyond
- *   the first 128 that took a workspace for them.
+ *   the first 128 that took a workspace for them.  A configuration passed back
+ *   from iqa_default_cfg is such a launch too, except captured on a stream on
+ *   which iqa_prepare was called with a configuration: that one is split.
  * Threads.  Every entry point may be called from several host threads at
  *   once, on the same stream or on different ones.  Calls on one stream run
  *   in the order they were enqueued, each launch finishing before the next

@@ -1729,6 +1729,7 @@ struct Workspace {
     void *ptr = nullptr;
     size_t cnt_bytes = 0;    // counter region, at ptr
     size_t part_bytes = 0;   // partial-sum region, at ptr + cnt_bytes
+    bool told = false;       // iqa_prepare was called on the stream with a configuration
 };
 std::mutex g_ws_mutex;
 std::map<std::tuple<int, void *, int, bool>, Workspace> g_ws;
@@ -1818,6 +1819,11 @@ constexpr size_t kCounterBytes = 64 << 10, kPartBytes = 128 << 10;
 constexpr int kMostOwn = 128;
 int g_own_buffers = 0;
 
+std::tuple<int, void *, int, bool> ws_key(int dev, hipStream_t s, bool own) {
+    const int thread = s == hipStreamPerThread ? t_thread.on(dev) : -1;
+    return std::make_tuple(dev, (void *)s, thread, own);
+}
+
 // *part receives the partial-sum region; the counter region ends where it
 // starts.  `own`: a buffer of the launches that can do without.  The caller
 // holds g_ws_mutex.
@@ -1825,8 +1831,7 @@ iqa_status workspace_for(hipStream_t s, bool own, const SplitNeed &need, float *
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_status(e);
-    const int thread = s == hipStreamPerThread ? t_thread.on(dev) : -1;
-    const auto key = std::make_tuple(dev, (void *)s, thread, own);
+    const auto key = ws_key(dev, s, own);
     if (own && g_own_buffers >= kMostOwn) {
         const auto it = g_ws.find(key);
         if (it == g_ws.end() || !it->second.ptr) return IQA_ERR_SCRATCH;
@@ -1873,6 +1878,16 @@ bool own_workspace(hipStream_t s, const SplitNeed &need, float **part) {
     (void)hipGetLastError();
     g_last_hip_error = err;
     return false;
+}
+
+// Whether the caller of launches on s has called iqa_prepare there with a
+// configuration, and so knows of the workspace that they share.
+bool prepared_with_cfg(hipStream_t s) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> lock(g_ws_mutex);
+    const auto it = g_ws.find(ws_key(dev, s, false));
+    return it != g_ws.end() && it->second.told;
 }
 
 // Scratch of the no-allocation entry point: a fixed array in device memory,
@@ -1985,6 +2000,11 @@ hipError_t launch_local(const KArgs &a, int mode, const iqa_launch_cfg &c, const
                   : launch_local_mode<false, false>(a, mode, c, g, s);
 }
 
+bool same_cfg(const iqa_launch_cfg &a, const iqa_launch_cfg &b) {
+    return a.vec == b.vec && a.waves == b.waves && a.unroll == b.unroll && a.seg == b.seg &&
+           a.rp == b.rp && a.ksplit == b.ksplit;
+}
+
 // Where a launch's split workspace comes from.
 enum class Ws {
     kLibrary,   // the per-(device, stream) buffer, grown on demand
@@ -1998,7 +2018,8 @@ enum class Ws {
 // a stream it has a buffer of its own there, which launches on that stream use
 // one after the other and no graph ever holds; captured, or through the
 // no-allocation entry point, it runs without a workspace (launch_local),
-// bitwise the same.
+// bitwise the same.  So does the default configuration passed back, unless
+// iqa_prepare was told of a configuration on that stream.
 iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, float C1,
                float C2, float C, float *lisi, float *aug, float *sums,
                const iqa_launch_cfg *cfg_in, void *stream, Ws ws, uint64_t *tl = nullptr) {
@@ -2018,9 +2039,12 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
     KArgs a{};
     const SplitNeed need = split_need(g, c);
     bool own = false, local = false;
-    if (c.ksplit > 1 && !cfg_in && local_ok(c, g) && !tuned_or_prepared(N, NT, c, x, y)) {
+    if (c.ksplit > 1 && (!cfg_in || (!tl && same_cfg(c, pick_cfg(N, NT, x, y)))) &&
+        local_ok(c, g) && !tuned_or_prepared(N, NT, c, x, y)) {
         own = true;
         local = ws == Ws::kScratch || (ws == Ws::kLibrary && capturing(s));
+        if (cfg_in && (ws == Ws::kPrepare || (ws == Ws::kLibrary && local && prepared_with_cfg(s))))
+            own = local = false;
     }
     // The workspace (or scratch) stays locked until the launches are
     // enqueued: a combine-mode split is two launches, and another host
@@ -2048,7 +2072,13 @@ iqa_status run(const float *x, const float *y, int64_t N, int64_t NT, float D, f
             }
         }
     }
-    if (ws == Ws::kPrepare) return IQA_OK;
+    if (ws == Ws::kPrepare) {
+        if (cfg_in && ws_lock.owns_lock()) {
+            int dev = 0;
+            if (hipGetDevice(&dev) == hipSuccess) g_ws[ws_key(dev, s, false)].told = true;
+        }
+        return IQA_OK;
+    }
 
     fill_pair(a, x, y, N, NT, D, C1, C2, C, lisi, aug, sums, c, g);
     a.smode = split_mode(g, c);

@@ -180,6 +180,45 @@ static int many_units(void) {
     return 0;
 }
 
+/* ---- the default configuration, asked for and passed back ---- */
+
+static int passed_back(void) {
+    int splits = 0;
+    uintptr_t stream = 1 << 12;
+    for (int64_t NT = 100; NT <= 2048; NT += 25) {
+        for (int64_t ns = 1; ns <= 16; ++ns, stream += 1 << 12) {
+            void *s = (void *)stream;
+            iqa_launch_cfg c;
+            CHECK(iqa_default_cfg(ns * NT, NT, X, Y, &c) == 0);
+            capturing = s;
+            const int by_rule = tiles_at(X, ns * NT, NT, NULL, s), before = launches;
+            const uint64_t items = last_items;
+            const int back = tiles_at(X, ns * NT, NT, &c, s);
+            capturing = NULL;
+            CHECK(back == by_rule);
+            if (by_rule == 0) CHECK(launches == before + 1 && last_items == items);
+            splits += c.ksplit > 1 && by_rule == 0;
+        }
+    }
+    CHECK(splits > 100 && captured_mallocs == 0);
+    /* Prepared with that configuration it is captured as it is launched. */
+    iqa_launch_cfg c;
+    void *s = (void *)stream;
+    CHECK(iqa_default_cfg(3000, 300, X, Y, &c) == 0 && c.ksplit > 1);
+    CHECK(tiles_at(X, 3000, 300, &c, s) == 0 && last_lds == 0);
+    const uint64_t split_items = last_items;
+    capturing = s;
+    CHECK(tiles_at(X, 3000, 300, &c, s) == 0 && last_lds > 0);
+    capturing = NULL;
+    CHECK(iqa_prepare(3000, 300, &c, s) == 0);
+    capturing = s;
+    CHECK(tiles_at(X, 3000, 300, &c, s) == 0 && last_lds == 0 && last_items == split_items);
+    CHECK(tiles_at(X, 3000, 300, NULL, s) == 0 && last_lds > 0);
+    CHECK(iqa_tiles_noalloc(X, Y, 3000, 300, 5e-7f, 1e-6f, 1e-6f, 1e-6f, OUT, OUT2, NULL, &c, s) == 0);
+    CHECK(last_lds > 0);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "per_thread")) return per_thread();
@@ -187,6 +226,7 @@ int main(int argc, char **argv) {
     if (!strcmp(name, "prepared")) return prepared();
     if (!strcmp(name, "sizes")) return sizes();
     if (!strcmp(name, "many_units")) return many_units();
+    if (!strcmp(name, "passed_back")) return passed_back();
     printf("no scenario %s\n", name);
     return 2;
 }

@@ -58,3 +58,8 @@ def test_the_largest_images_can_be_launched(program):
 def test_batches_of_any_number_of_units_can_be_launched(program):
     """The batch kernels are persistent: their grid is capped, not refused."""
     scenario(program, "many_units")
+
+
+def test_default_configuration_passed_back_is_the_default_launch(program):
+    """iqa_tiles_cfg with what iqa_default_cfg returned is captured as iqa_tiles is."""
+    scenario(program, "passed_back")
