@@ -2474,6 +2474,7 @@ iqa_status iqa_pyramid(const float *sums_in, int64_t ns, int64_t levels, float D
     if (!sums_in) return IQA_ERR_NULL;
     if (ns <= 0 || ns > IQA_MAX_N || levels < 1 || levels > 17 || ns % (int64_t(1) << levels) != 0)
         return IQA_ERR_SHAPE;
+    if ((ns / 2) * (ns / 2) > INT_MAX) return IQA_ERR_SHAPE;   // as a merge of the first level
     if (!lisi || !auglisi || !sums_out) return IQA_ERR_NULL;
     if (!aligned(sums_in, 16)) return IQA_ERR_ALIGN;
     for (int64_t l = 0; l < levels; ++l) {

@@ -219,6 +219,24 @@ static int passed_back(void) {
     return 0;
 }
 
+/* ---- a pyramid takes the levels that the chain of merges takes ---- */
+
+static int pyramid_sizes(void) {
+    float *out[17];
+    for (int i = 0; i < 17; ++i) out[i] = OUT;
+    for (int64_t ns = 2; ns <= 1 << 17; ns += ns < 90000 ? 2 * (1 + ns / 64) : 2) {
+        const int one = iqa_merge_tiles(X, ns, 2, 5e-7f, 1e-6f, 1e-6f, OUT, OUT2, OUT, NULL);
+        const int st = iqa_pyramid(X, ns, 1, 5e-7f, 1e-6f, 1e-6f, out, out, out, NULL);
+        if (st != one) {
+            printf("%d: %s, and %s\n", (int)ns, iqa_status_str(st), iqa_status_str(one));
+            return 1;
+        }
+    }
+    CHECK(iqa_pyramid(X, 1 << 17, 17, 5e-7f, 1e-6f, 1e-6f, out, out, out, NULL) == IQA_ERR_SHAPE);
+    CHECK(iqa_pyramid(X, 1 << 16, 16, 5e-7f, 1e-6f, 1e-6f, out, out, out, NULL) == IQA_OK);
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "per_thread")) return per_thread();
@@ -227,6 +245,7 @@ int main(int argc, char **argv) {
     if (!strcmp(name, "sizes")) return sizes();
     if (!strcmp(name, "many_units")) return many_units();
     if (!strcmp(name, "passed_back")) return passed_back();
+    if (!strcmp(name, "pyramid_sizes")) return pyramid_sizes();
     printf("no scenario %s\n", name);
     return 2;
 }

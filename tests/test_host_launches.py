@@ -63,3 +63,8 @@ def test_batches_of_any_number_of_units_can_be_launched(program):
 def test_default_configuration_passed_back_is_the_default_launch(program):
     """iqa_tiles_cfg with what iqa_default_cfg returned is captured as iqa_tiles is."""
     scenario(program, "passed_back")
+
+
+def test_pyramid_refuses_what_the_chain_of_merges_refuses(program):
+    """More than 2^31 - 1 tiles in a level: IQA_ERR_SHAPE."""
+    scenario(program, "pyramid_sizes")
