@@ -62,10 +62,10 @@ def _check_images(x: torch.Tensor, y: torch.Tensor) -> int:
     return int(x.shape[0])
 
 
-def _stream_handle(device: torch.device, stream):
+def _stream_handle(device, stream):
     if stream is None:
         # The current stream's handle without a Stream object around it (2.0 us).
-        if device.index is not None:
+        if type(device) is torch.device and device.index is not None:
             return _cuda_getCurrentRawStream(device.index)
         stream = torch.cuda.current_stream(device)
     if isinstance(stream, torch.cuda.Stream):
@@ -73,10 +73,11 @@ def _stream_handle(device: torch.device, stream):
     return int(stream)
 
 
-def _on_device(device: torch.device, fn, *args) -> int:
-    """``fn(*args)`` with ``device`` current.  The context manager takes 1.3 us,
-    so it is entered only where another device is."""
-    if device.index == _cuda_getDevice():
+def _on_device(device, fn, *args) -> int:
+    """``fn(*args)`` with ``device`` (whatever torch.cuda.device takes) current.
+    The context manager takes 1.3 us, so it is entered only where another device
+    is, or may be."""
+    if type(device) is torch.device and device.index == _cuda_getDevice():
         return fn(*args)
     with torch.cuda.device(device):
         return fn(*args)
