@@ -13,10 +13,14 @@ from typing import Dict, NamedTuple, Optional
 
 import numpy as np
 import torch
-from torch._C import _cuda_getCurrentRawStream, _cuda_getDevice
 
 from . import _lib
 from ._lib import IqaError, LaunchCfg
+
+# What torch.cuda calls for the current stream and device, without the objects
+# around it; a torch without GPU support has neither.
+_cuda_getCurrentRawStream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_cuda_getDevice = getattr(torch._C, "_cuda_getDevice", lambda: -1)
 
 # The paper only asks C1, C2, C << 1; these defaults are 1e-6 each and D is
 # C1/2, the choice for which identical tiles give LISI = S/(S + C2) ~ 1.
@@ -65,7 +69,7 @@ def _check_images(x: torch.Tensor, y: torch.Tensor) -> int:
 def _stream_handle(device, stream):
     if stream is None:
         # The current stream's handle without a Stream object around it (2.0 us).
-        if type(device) is torch.device and device.index is not None:
+        if type(device) is torch.device and device.index is not None and _cuda_getCurrentRawStream:
             return _cuda_getCurrentRawStream(device.index)
         stream = torch.cuda.current_stream(device)
     if isinstance(stream, torch.cuda.Stream):
