@@ -71,6 +71,8 @@ def _stream_handle(device, stream):
         # The current stream's handle without a Stream object around it (2.0 us).
         if type(device) is torch.device and device.index is not None and _cuda_getCurrentRawStream:
             return _cuda_getCurrentRawStream(device.index)
+        if type(device) is torch.device and device.type != "cuda":   # before any look for a GPU
+            raise ValueError(f"Expected a cuda device, but got: {device}")
         stream = torch.cuda.current_stream(device)
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
@@ -81,7 +83,8 @@ def _on_device(device, fn, *args) -> int:
     """``fn(*args)`` with ``device`` (whatever torch.cuda.device takes) current.
     The context manager takes 1.3 us, so it is entered only where another device
     is, or may be."""
-    if type(device) is torch.device and device.index == _cuda_getDevice():
+    if type(device) is torch.device and device.index is not None and \
+            device.index == _cuda_getDevice():
         return fn(*args)
     with torch.cuda.device(device):
         return fn(*args)

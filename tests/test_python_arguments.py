@@ -60,3 +60,10 @@ def test_the_package_imports_on_a_torch_without_gpu_support():
         "else:\n"
         "    raise AssertionError('ran without a GPU')\n")
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+
+
+@pytest.mark.parametrize("stream", [None, 0])
+def test_sums_in_host_memory_are_refused_as_such(stream):
+    """Also where there is no GPU: the words are about the tensor."""
+    with pytest.raises(ValueError, match="Expected a cuda device, but got: cpu"):
+        iqa.merge_tiles(torch.zeros(4, 4), 2, stream=stream)
