@@ -42,7 +42,7 @@ class Batch:
     N x N device tensors.  Pairs with NT % 4 == 0 and 16-byte aligned images go
     into the persistent launch; the others share a launch that does what a
     launch of iqa_tiles each would, or are launched one by one (tiles split over
-    workgroups, N_T < 4), on the same stream.  Output tensors are allocated here
+    workgroups, N_T < 4, batches made under capture), on the same stream.  Output tensors are allocated here
     and reused by every run: ``results[i]`` is the :class:`TileResult` of pair i.
     """
 
@@ -108,7 +108,8 @@ class Batch:
         odd = [i for i in self.single if self.inputs[i][0].device == self.out.device and
                self._describe(lib.iqa_odd_batch_describe, [i])[0] == 0]
         self.odd_count, self.odd_units, self.odd_descs = 0, 0, None
-        if len(odd) > 1:
+        # Their table is copied to the device, which a capture does not allow.
+        if len(odd) > 1 and not torch.cuda.is_current_stream_capturing():
             st, host, units = self._describe(lib.iqa_odd_batch_describe, odd)
             if st == 0:
                 self.odd_count, self.odd_units = len(odd), units
