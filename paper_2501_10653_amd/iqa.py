@@ -68,9 +68,11 @@ def _check_images(x: torch.Tensor, y: torch.Tensor) -> int:
 
 def _stream_handle(device, stream):
     if stream is None:
-        # The current stream's handle without a Stream object around it (2.0 us).
-        if type(device) is torch.device and device.index is not None and _cuda_getCurrentRawStream:
-            return _cuda_getCurrentRawStream(device.index)
+        # The current stream's handle without a Stream object around it (2.0 us),
+        # for a torch.device with an index; whatever else torch takes goes to it.
+        index = getattr(device, "index", None)
+        if type(index) is int and _cuda_getCurrentRawStream:
+            return _cuda_getCurrentRawStream(index)
         if type(device) is torch.device and device.type != "cuda":   # before any look for a GPU
             raise ValueError(f"Expected a cuda device, but got: {device}")
         stream = torch.cuda.current_stream(device)
@@ -83,8 +85,8 @@ def _on_device(device, fn, *args) -> int:
     """``fn(*args)`` with ``device`` (whatever torch.cuda.device takes) current.
     The context manager takes 1.3 us, so it is entered only where another device
     is, or may be."""
-    if type(device) is torch.device and device.index is not None and \
-            device.index == _cuda_getDevice():
+    index = getattr(device, "index", None)
+    if type(index) is int and index == _cuda_getDevice():
         return fn(*args)
     with torch.cuda.device(device):
         return fn(*args)
