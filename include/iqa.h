@@ -72,8 +72,8 @@
  * Preconditions that are not checked: pixels are finite or NaN (not +-Inf) and
  *   of magnitude at most 2^50, so that the per-tile sums stay finite in FP32.
  * Precision.  Per-pixel terms are FP32; tile sums are Kahan-compensated FP32;
- *   augLISI is finalised in double-float arithmetic; the final quotients are
- *   within one unit in the last place.  Worst-case error against exact
+ *   LISI and augLISI are finalised in double-float arithmetic: LISI is within
+ *   0.51 units in the last place of Eq. (1) of the FP32 sums.  Worst-case error against exact
  *   arithmetic: about 3.6e-6 (61 units of FP32 roundoff) relative to the
  *   value for the sums and LISI, and relative to max(|augLISI|,
  *   P/(Sx+Sy+C)) for augLISI; measured: below 6e-7.  Results are bitwise

@@ -18,11 +18,11 @@
 //     for shapes with few large tiles several workgroups share them (the last
 //     of them to finish combines their partials, chosen by an atomic ticket; no
 //     second launch).
-//   * Each lane folds `vec` adjacent pixels with plain FP32 (FMA chains) and
-//     adds the block into Kahan-compensated (hi, lo) accumulators: the long
-//     per-lane sums are compensated.  Across lanes the partial sums are folded
-//     to one float and added plainly: every partial is non-negative, so a tree
-//     of depth d adds at most d units of roundoff, relative.
+//   * Each lane folds up to 16 pixels with plain FP32 (FMA chains) and adds the
+//     block into Kahan-compensated (hi, lo) accumulators: the long per-lane sums
+//     are compensated.  Across lanes the partial sums are folded to one float
+//     and added plainly: every partial is non-negative, so a tree of depth d
+//     adds at most d units of roundoff, relative.
 //   * Loads are double-buffered: the next `unroll` rows are in flight while the
 //     current ones are reduced.
 //   * Every reduction has a fixed order and there are no floating-point
@@ -237,6 +237,42 @@ __device__ __forceinline__ Sum4 fold(const Acc &a) {
     return Sum4{a.A.hi + a.A.lo, a.P.hi + a.P.lo, a.X.hi + a.X.lo, a.Y.hi + a.Y.lo};
 }
 
+// The same steps for sums in FP64.
+struct Sum4d {
+    double A, P, X, Y;
+};
+
+template <int MODE, typename Step>
+__device__ __forceinline__ void each(Sum4d &s, Step step) {
+    if constexpr ((MODE & kLisi) != 0) step(s.A);
+    if constexpr ((MODE & kAug) != 0) step(s.P);
+    step(s.X);
+    step(s.Y);
+}
+
+__device__ __forceinline__ double with_words(float hi, float lo) {
+    return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+}
+
+template <int MODE, int CTRL>
+__device__ __forceinline__ void lanes_add(Sum4d &s) {
+    each<MODE>(s, [](double &v) {
+        v += with_words(dpp<CTRL>(__int_as_float(__double2hiint(v))),
+                        dpp<CTRL>(__int_as_float(__double2loint(v))));
+    });
+}
+
+template <int MODE, int W>
+__device__ __forceinline__ void lanes_swap_add(Sum4d &s) {
+    each<MODE>(s, [](double &v) {
+        float h0 = __int_as_float(__double2hiint(v)), h1 = h0;
+        float l0 = __int_as_float(__double2loint(v)), l1 = l0;
+        permlane_swap<W>(h0, h1);
+        permlane_swap<W>(l0, l1);
+        v = with_words(h0, l0) + with_words(h1, l1);
+    });
+}
+
 // ---------------------------------------------------------------------------
 // Per-pixel work
 // ---------------------------------------------------------------------------
@@ -295,29 +331,39 @@ __device__ __forceinline__ float velem(const typename VecT<VEC>::T &v, int e) {
     }
 }
 
-// Per-pixel terms of VEC adjacent pixel pairs, added with plain FP32 (FMA
-// chains) into a short block sum b.  A pair of zeros adds nothing.  SKIP: the
-// first `skip` elements are not counted (the clamp's threshold is infinite).
+// Per-pixel terms of VEC adjacent pixel pairs, added to a short block sum b in
+// plain FP32: products as FMA chains, the four pixels of a quad in pairs first.  A
+// pair of zeros adds nothing.  SKIP: the first `skip` elements are not counted
+// (the clamp's threshold is infinite).
 template <int VEC, int MODE, bool SKIP = false>
 __device__ __forceinline__ void accumulate(const typename VecT<VEC>::T &xv,
                                            const typename VecT<VEC>::T &yv, float C1, Sum4 &b,
                                            int skip = 0) {
+    float xc[VEC], yc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         const float xr = velem<VEC>(xv, e);
         const float yr = velem<VEC>(yv, e);
         const float floor = SKIP && e < skip ? __builtin_inff() : 0.f;
-        const float xc = xr > floor ? xr : 0.f;   // Sec. 2 clamp; NaN and -0 -> +0
-        const float yc = yr > floor ? yr : 0.f;
-        const float s = xc + yc;                // |x'+y'| (both non-negative)
-        const float d = fabsf(xc - yc);         // |x'-y'|
+        xc[e] = xr > floor ? xr : 0.f;   // Sec. 2 clamp; NaN and -0 -> +0
+        yc[e] = yr > floor ? yr : 0.f;
+        const float s = xc[e] + yc[e];          // |x'+y'| (both non-negative)
+        const float d = fabsf(xc[e] - yc[e]);   // |x'-y'|
         if constexpr ((MODE & kLisi) != 0) {
             const float r = __builtin_amdgcn_rcpf(d + C1);
             b.A = __builtin_fmaf(s, r, b.A);
         }
         if constexpr ((MODE & kAug) != 0) b.P = __builtin_fmaf(s, d, b.P);
-        b.X = b.X + xc;
-        b.Y = b.Y + yc;
+    }
+    if constexpr (VEC == 4) {
+        b.X += (xc[0] + xc[1]) + (xc[2] + xc[3]);
+        b.Y += (yc[0] + yc[1]) + (yc[2] + yc[3]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            b.X += xc[e];
+            b.Y += yc[e];
+        }
     }
 }
 
@@ -337,11 +383,20 @@ __device__ __forceinline__ void add_block(Acc &acc, const Sum4 &b) {
 // A tile's sums reach these as plain FP32 values: each lane folded its
 // compensation in before the cross-lane adds.
 
-// Eq. 1.
+// Eq. 1, with the roundings of the numerator and the denominator corrected in the
+// quotient (as plain FP32 operations they were most of LISI's error: 2048^2/64 rms
+// 1.19 units of roundoff, 1.06 so).
 __device__ __forceinline__ void finalize_lisi(const PairArgs &a, int64_t t, const Sum4 &s) {
     if (!a.lisi) return;
-    const float den = fmaxf(s.X, s.Y) + a.C2;
-    a.lisi[t] = div_pos(a.D * s.A, den, __builtin_amdgcn_rcpf(den));
+    float d, dl;
+    two_sum(fmaxf(s.X, s.Y), a.C2, d, dl);
+    const float n = a.D * s.A;
+    const float nl = __builtin_fmaf(a.D, s.A, -n);
+    const float rd = __builtin_amdgcn_rcpf(d);
+    const float q = n * rd;
+    float r = __builtin_fmaf(-q, d, n);   // remainder of (n + nl) / (d + dl)
+    r += __builtin_fmaf(-q, dl, nl);
+    a.lisi[t] = __builtin_fmaf(r, rd, q);
 }
 
 // Eq. 2: S = Sx + Sy + C and q = P / S in double-float, then 1 - q.
@@ -440,10 +495,13 @@ __device__ __forceinline__ uint64_t stamp_after(float v) {
 // loads: 3000^2/300 15.7 against 17.0 us.)
 //
 // Items are read in batches of U with the next batch in flight while the
-// current one is reduced; each batch is one block of plain FP32 sums
-// (compensation is per batch).  Items beyond a multiple of U form a batch of
-// their own that goes first, so every load has others in flight with it; the
-// item that some lanes lack is always in it.
+// current one is reduced, in blocks of kBlock items of plain FP32 sums between
+// two compensated additions.  Items beyond a multiple of U form a batch of their
+// own that goes first, so every load has others in flight with it; the item that
+// some lanes lack is always in it.  It is often all that a lane has, and is
+// reduced in blocks of two.  (Compensating every item costs 1.5% at 2025^2/45 and
+// 3000^2/100; blocks of eight, 32 pixels, raise the rms error of the sums at
+// 8192^2/16 from 0.72 units of roundoff to 0.84.)
 //
 // ANY (VEC 4): images at any float address and any NT >= 4.  A lane loads a
 // quad wherever it lies; the last quad of a tile row is moved back to end with
@@ -454,6 +512,7 @@ __device__ __forceinline__ uint64_t stamp_after(float v) {
 // 85.8, 500^2/50 5.0 and 4.0, 1000^2/250 6.2 and 5.5; 2000^2/50 8.1 both;
 // 2025^2/25 7.6 and 8.3, 3000^2/75 15.4 and 16.1.  Two waves lie between.)
 constexpr int kAnyWaves = 4;
+constexpr int kBlock = 4;
 
 template <int VEC, bool ANY, int U, int MODE, bool WRAP, bool TL = false>
 __device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, int slice, int lane,
@@ -547,16 +606,19 @@ __device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, i
 #pragma unroll
             for (int u = 0; u < U; ++u) load_item(xv[u], yv[u], true, u, last);
         };
-        auto reduce_item = [&](const V &xv, const V &yv, int u, uint32_t last, Sum4 &b) {
+        auto quad = [&](const V (&xv)[U], const V (&yv)[U], uint32_t last, int u, Sum4 &b) {
             int sk = skip;
             if constexpr (ANY && WRAP) sk = (last >> u) & 1 ? over : 0;
-            accumulate<VEC, MODE, ANY>(xv, yv, a.C1, b, sk);
+            accumulate<VEC, MODE, ANY>(xv[u], yv[u], a.C1, b, sk);
         };
         auto reduce = [&](const V (&xv)[U], const V (&yv)[U], uint32_t last) {
-            Sum4 b{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < U; ++u) reduce_item(xv[u], yv[u], u, last, b);
-            add_block<MODE>(acc, b);
+            for (int u = 0; u < U; u += kBlock) {
+                Sum4 b{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int v = u; v < u + kBlock; ++v) quad(xv, yv, last, v, b);
+                add_block<MODE>(acc, b);
+            }
         };
         // Full batches, and the items of the partial one (0..U).
         using Count = std::conditional_t<WRAP, uint64_t, uint32_t>;
@@ -573,11 +635,14 @@ __device__ __forceinline__ Sum4 slice_sums(const PairArgs &a, int ty, int txg, i
         }
         if (left) load(ax, ay, alast);
         if (part) {
-            Sum4 b{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (u < part) reduce_item(cx[u], cy[u], u, clast, b);
-            add_block<MODE>(acc, b);
+            for (int u = 0; u < U; u += 2) {
+                if (u >= part) break;
+                Sum4 b{0.f, 0.f, 0.f, 0.f};
+                quad(cx, cy, clast, u, b);
+                if (u + 1 < part) quad(cx, cy, clast, u + 1, b);
+                add_block<MODE>(acc, b);
+            }
             if constexpr (TL) ts[0] = stamp_after(acc.X.hi);
         }
         if (left) {
@@ -618,6 +683,41 @@ __device__ __forceinline__ float4 wave_tree(float4 (&v)[WAVES]) {
         }
     }
     return v[0];
+}
+
+// One wave finishes the tiles of a group from the waves' sums in LDS, lane j tile
+// j.  Quads at any address and the smallest tiles have more waves on a tile than
+// compensation alone would ask for, so their sums are added without further
+// roundoff: a quad of lanes per tile, one of the four sums each, in FP64 (2025^2/45:
+// rms errors of P and Sx 0.82 and 0.71 units of roundoff as a tree, 0.68 and 0.60
+// so, and 0.1 us of 8.2; 2024^2/8 A 0.79 and 0.68, and 0.3 us of 7.3).
+template <bool ANY, int WAVES, typename Finish>
+__device__ __forceinline__ void finish_group(const PairArgs &a, const float4 (&lds)[WAVES][kWave],
+                                             int ty, int txg, int lane, Finish finish) {
+    const int ht = tiles_per_wave(a);
+    if (ANY || a.log_grp <= 2) {
+        for (int j0 = 0; j0 < ht; j0 += kWave / 4) {
+            const int j = j0 + (lane >> 2), tx = txg * ht + j;
+            const bool mine = j < ht && tx < a.ns;
+            double v = 0.0;
+            if (mine) {
+                const float *w = reinterpret_cast<const float *>(&lds[0][j]) + (lane & 3);
+#pragma unroll
+                for (int i = 0; i < WAVES; ++i) v += (double)w[i * kWave * 4];
+            }
+            const float s = (float)v;
+            const Sum4 r{s, dpp<0x55>(s), dpp<0xAA>(s), dpp<0xFF>(s)};   // of the quad's lanes
+            if (mine && (lane & 3) == 0) finish((int64_t)ty * a.ns + tx, r);
+        }
+    } else {
+        const int tx = txg * ht + lane;
+        if (lane >= ht || tx >= a.ns) return;
+        float4 w[WAVES];
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) w[i] = lds[i][lane];
+        const float4 v = wave_tree<WAVES>(w);
+        finish((int64_t)ty * a.ns + tx, Sum4{v.x, v.y, v.z, v.w});
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -690,6 +790,50 @@ __device__ __forceinline__ void wait_vmem() {
     __builtin_amdgcn_s_waitcnt(/*vmcnt*/ 0 | (/*expcnt*/ 0x7 << 4) | (/*lgkmcnt*/ 0xf << 8));
 }
 
+// Add up n parts of a tile, part(p), over its 2^log_g lanes (q: the lane's place
+// among them); the first of them ends with the sums.  A power of two of parts:
+// lane q has parts q, q + lanes, ..., and the lanes' tree is even.  Else that tree
+// would be lopsided, and its error that of up to log2(n) additions of nearly the
+// whole (3000^2/300 in five parts: the sums' rms error 12% above that of one
+// workgroup): a quarter to a half as many lanes, two to four parts each, in FP64.
+template <int MODE, typename Part>
+__device__ __forceinline__ Sum4 parts_sum(int n, int log_g, int q, Part part) {
+    const int log_n = 31 - __clz(n);
+    if (n == 1 << log_n) {
+        Acc c = acc_zero();
+        for (int p = q; p < n; p += 1 << log_g) {
+            const float4 w = part(p);
+            if constexpr ((MODE & kLisi) != 0) cadd(c.A, w.x);
+            if constexpr ((MODE & kAug) != 0) cadd(c.P, w.y);
+            cadd(c.X, w.z);
+            cadd(c.Y, w.w);
+        }
+        return group_allreduce<MODE>(fold(c), min(log_g, log_n));
+    }
+    const int log_l = min(log_g, log_n - 1), lanes = 1 << log_l;
+    Sum4d d{0.0, 0.0, 0.0, 0.0};
+    for (int from = q; q < lanes && from < n; from += 4 * lanes) {
+        float4 w[4];   // loads in flight
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            w[i] = from + i * lanes < n ? part(from + i * lanes) : float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr ((MODE & kLisi) != 0) d.A += w[i].x;
+            if constexpr ((MODE & kAug) != 0) d.P += w[i].y;
+            d.X += w[i].z;
+            d.Y += w[i].w;
+        }
+    }
+    if (log_l > 0) lanes_add<MODE, 0xB1>(d);
+    if (log_l > 1) lanes_add<MODE, 0x4E>(d);
+    if (log_l > 2) lanes_add<MODE, 0x141>(d);
+    if (log_l > 3) lanes_add<MODE, 0x140>(d);
+    if (log_l > 4) lanes_swap_add<MODE, 16>(d);
+    if (log_l > 5) lanes_swap_add<MODE, 32>(d);
+    return Sum4{(float)d.A, (float)d.P, (float)d.X, (float)d.Y};
+}
+
 // Add up tile group grp's parts and finalise its tiles (one wave).  COHERENT
 // reads the partials with device-coherent loads (within the launch that wrote
 // them), else with plain loads (a later launch).
@@ -700,25 +844,14 @@ __device__ __forceinline__ void combine_parts(const KArgs &a, int grp, int lane)
     const int64_t pitch = part_entries(a.smode, tiles_per_wave(a));
     const int ty = udiv(grp, a.ngx_m, a.ngx);
     const int txg = grp - ty * a.ngx;
-    // Lane group of tile j: 2^log_grp lanes; lane q of the group takes parts
-    // q, q + g, ...
-    const int g = 1 << a.log_grp;
-    const int j = lane >> a.log_grp;
-    const int q = lane & (g - 1);
-    const int ht = tiles_per_wave(a);
-    const int tx = txg * ht + j;
-    Acc c = acc_zero();
-    if (tx < a.ns) {
-        for (int p = q; p < a.ks; p += g) {
-            const float4 *src = ws + (base + p) * pitch + j;
-            const float4 w = COHERENT ? load_coherent(src) : *src;
-            if constexpr ((MODE & kLisi) != 0) cadd(c.A, w.x);
-            if constexpr ((MODE & kAug) != 0) cadd(c.P, w.y);
-            cadd(c.X, w.z);
-            cadd(c.Y, w.w);
-        }
-    }
-    const Sum4 s = group_allreduce<MODE>(fold(c), a.log_grp);
+    const int j = lane >> a.log_grp;   // the lane group's tile
+    const int q = lane & ((1 << a.log_grp) - 1);
+    const int tx = txg * tiles_per_wave(a) + j;
+    const Sum4 s = parts_sum<MODE>(a.ks, a.log_grp, q, [&](int p) {
+        if (tx >= a.ns) return float4{0.f, 0.f, 0.f, 0.f};
+        const float4 *src = ws + (base + p) * pitch + j;
+        return COHERENT ? load_coherent(src) : *src;
+    });
     if (q == 0 && tx < a.ns) finalize<MODE>(a, (int64_t)ty * a.ns + tx, s);
 }
 
@@ -785,44 +918,44 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     const Sum4 s = slice_sums<VEC, ANY, U, MODE, WRAP, TL>(a, ty, txg, part * WAVES + wave, lane, ts + 1);
     constexpr bool kTwoWaveFinish = WAVES > 1 && MODE == kBoth && !SPLIT;
 
-    // The tile this lane finishes, if any: a lane group's leader with one wave
-    // per workgroup; lane j of wave 0 after the LDS combine otherwise.
-    bool mine;
-    int jt;
     float4 v{s.A, s.P, s.X, s.Y};
+    bool last = true;   // this workgroup finished its tiles
     if constexpr (WAVES == 1) {
-        jt = lane >> a.log_grp;
-        mine = (lane & ((1 << a.log_grp) - 1)) == 0 && txg * ht + jt < a.ns;
+        // A lane group's leader has its tile's sums.
+        const int jt = lane >> a.log_grp;
+        const bool mine = (lane & ((1 << a.log_grp) - 1)) == 0 && txg * ht + jt < a.ns;
+        if constexpr (SPLIT) {
+            last = split_finish<MODE>(a, grp, part, lane, mine, jt, v);
+        } else {
+            if (mine) finalize<MODE>(a, (int64_t)ty * a.ns + txg * ht + jt, s);
+        }
     } else {
         // Combine the waves' slices of each tile in LDS, wave order fixed.
         __shared__ float4 lds[WAVES][kWave];
         if ((lane & ((1 << a.log_grp) - 1)) == 0) lds[wave][lane >> a.log_grp] = v;
         __syncthreads();
         if (wave != 0 && !(kTwoWaveFinish && wave == 1)) return;
-        jt = lane;
-        mine = lane < ht && txg * ht + lane < a.ns;
-        if (mine) {
-            float4 w[WAVES];
+        if constexpr (SPLIT) {
+            const bool mine = lane < ht && txg * ht + lane < a.ns;
+            if (mine) {
+                float4 w[WAVES];
 #pragma unroll
-            for (int i = 0; i < WAVES; ++i) w[i] = lds[i][lane];
-            v = wave_tree<WAVES>(w);
-        }
-    }
-    bool last = true;   // this workgroup finished its tiles
-    if constexpr (!SPLIT) {
-        const int64_t t = (int64_t)ty * a.ns + txg * ht + jt;
-        const Sum4 r{v.x, v.y, v.z, v.w};
-        if constexpr (kTwoWaveFinish) {
-            if (mine && wave == 0) {
-                finalize_lisi(a, t, r);
-                store_sums(a, t, r);
+                for (int i = 0; i < WAVES; ++i) w[i] = lds[i][lane];
+                v = wave_tree<WAVES>(w);
             }
-            if (mine && wave == 1) finalize_aug(a, t, r);
+            last = split_finish<MODE>(a, grp, part, lane, mine, lane, v);
         } else {
-            if (mine) finalize<MODE>(a, t, r);
+            finish_group<ANY>(a, lds, ty, txg, lane, [&](int64_t t, const Sum4 &r) {
+                if constexpr (!kTwoWaveFinish) {
+                    finalize<MODE>(a, t, r);
+                } else if (wave == 0) {
+                    finalize_lisi(a, t, r);
+                    store_sums(a, t, r);
+                } else {
+                    finalize_aug(a, t, r);
+                }
+            });
         }
-    } else {
-        last = split_finish<MODE>(a, grp, part, lane, mine, jt, v);
     }
     if constexpr (TL) {
         if (wave == 0) {
@@ -843,8 +976,12 @@ __device__ __forceinline__ void tiles_body(const KArgs &a, uint64_t *tl) {
     }
 }
 
+// Batches of four leave room for five waves per SIMD, which small tiles need (at
+// four, 3260^2/10 takes 18.3 us, and 16.3 with five); where the loop needs more
+// registers than that (ANY with WRAP or SPLIT) they would go to memory.
 template <int VEC, bool ANY, int WAVES, int U, int MODE, bool WRAP, bool SPLIT>
-__global__ __launch_bounds__(WAVES * kWave) void tiles_kernel(KArgs a) {
+__global__ __launch_bounds__(WAVES * kWave, U == 4 && !(ANY && (WRAP || SPLIT)) ? 5 : 1) void
+tiles_kernel(KArgs a) {
     tiles_body<VEC, ANY, WAVES, U, MODE, WRAP, SPLIT, false>(a, nullptr);
 }
 
@@ -873,24 +1010,20 @@ __global__ __launch_bounds__(kLocalWaves * kWave) void tiles_local_kernel(KArgs 
     }
     __syncthreads();
     if (wave != 0) return;
-    Acc c = acc_zero();
-    for (int p = lane; p < a.ks; p += kWave) {
-        float4 v = slices[p * waves];
+    const Sum4 s = parts_sum<MODE>(a.ks, 6, lane, [&](int p) {
+        const float4 *v = slices + p * waves;
         if (waves == 4) {
-            float4 w[4] = {v, slices[p * 4 + 1], slices[p * 4 + 2], slices[p * 4 + 3]};
-            v = wave_tree<4>(w);
-        } else if (waves == 8) {
+            float4 w[4] = {v[0], v[1], v[2], v[3]};
+            return wave_tree<4>(w);
+        }
+        if (waves == 8) {
             float4 w[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) w[i] = slices[p * 8 + i];
-            v = wave_tree<8>(w);
+            for (int i = 0; i < 8; ++i) w[i] = v[i];
+            return wave_tree<8>(w);
         }
-        if constexpr ((MODE & kLisi) != 0) cadd(c.A, v.x);
-        if constexpr ((MODE & kAug) != 0) cadd(c.P, v.y);
-        cadd(c.X, v.z);
-        cadd(c.Y, v.w);
-    }
-    const Sum4 s = group_allreduce<MODE>(fold(c), a.log_grp);
+        return v[0];
+    });
     if (lane == 0) finalize<MODE>(a, (int64_t)ty * a.ns + tx, s);
 }
 
@@ -990,7 +1123,8 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
             const Sum4 s = batch_wrap(a) ? slice_sums<4, false, U, kBoth, true>(a, ty, txg, 0, lane)
                                      : slice_sums<4, false, U, kBoth, false>(a, ty, txg, 0, lane);
             const int tx = txg * tiles_per_wave(a) + (lane >> a.log_grp);
-            if (leader && tx < a.ns) finalize<kBoth>(a, (int64_t)ty * a.ns + tx, s);
+            if (leader && tx < a.ns)
+                finalize<kBoth>(a, (int64_t)ty * a.ns + tx, s);
         } else {
             // Workgroup-uniform branch: every wave reaches both barriers.
             const int grp = (int)g64;
@@ -1001,24 +1135,15 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
             if (leader) lds[wave][lane >> a.log_grp] = float4{s.A, s.P, s.X, s.Y};
             __syncthreads();
             // Two waves finish the tiles at once, as in the tile kernel.
-            const int ht = tiles_per_wave(a);
-            if (wave < 2 && lane < ht) {
-                const int txl = txg * ht + lane;
-                if (txl < a.ns) {
-                    float4 v[kBatchWaves];
-#pragma unroll
-                    for (int w = 0; w < kBatchWaves; ++w) v[w] = lds[w][lane];
-                    const float4 t4 = wave_tree<kBatchWaves>(v);
-                    const Sum4 r{t4.x, t4.y, t4.z, t4.w};
-                    const int64_t t = (int64_t)ty * a.ns + txl;
+            if (wave < 2)
+                finish_group<ODD>(a, lds, ty, txg, lane, [&](int64_t t, const Sum4 &r) {
                     if (wave == 0) {
                         finalize_lisi(a, t, r);
                         store_sums(a, t, r);
                     } else {
                         finalize_aug(a, t, r);
                     }
-                }
-            }
+                });
             __syncthreads();   // the LDS slots are reused by the next unit
         }
     }
@@ -1124,7 +1249,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_small_kernel(MergeArgs m,
     }
     const float4 w = wave_tree<LOADS>(v);
     const Sum4 s = group_allreduce<kBoth>(Sum4{w.x, w.y, w.z, w.w}, log_g);
-    if (q == 0) finalize_merge(m.D, m.C2, m.C, m.lisi, m.aug, m.sums, p, s);
+    if (q == 0)
+        finalize_merge(m.D, m.C2, m.C, m.lisi, m.aug, m.sums, p, s);
 }
 
 // f above 16.  A parent's children are cut into `parts` runs of
@@ -1181,15 +1307,7 @@ __device__ __forceinline__ float4 merge_run(const MergeArgs &m, int64_t p, int p
 // The runs' sums of one parent, added by one wave.
 template <typename Run>
 __device__ __forceinline__ void merge_runs(const MergeArgs &m, int64_t p, int lane, Run run) {
-    Acc c = acc_zero();
-    for (int i = lane; i < m.parts; i += kWave) {
-        const float4 w = run(i);
-        cadd(c.A, w.x);
-        cadd(c.P, w.y);
-        cadd(c.X, w.z);
-        cadd(c.Y, w.w);
-    }
-    const Sum4 s = group_allreduce<kBoth>(fold(c), 6);
+    const Sum4 s = parts_sum<kBoth>(m.parts, 6, lane, run);
     if (lane == 0) finalize_merge(m.D, m.C2, m.C, m.lisi, m.aug, m.sums, p, s);
 }
 
