@@ -262,17 +262,6 @@ __device__ __forceinline__ void lanes_add(Sum4d &s) {
     });
 }
 
-template <int MODE, int W>
-__device__ __forceinline__ void lanes_swap_add(Sum4d &s) {
-    each<MODE>(s, [](double &v) {
-        float h0 = __int_as_float(__double2hiint(v)), h1 = h0;
-        float l0 = __int_as_float(__double2loint(v)), l1 = l0;
-        permlane_swap<W>(h0, h1);
-        permlane_swap<W>(l0, l1);
-        v = with_words(h0, l0) + with_words(h1, l1);
-    });
-}
-
 // ---------------------------------------------------------------------------
 // Per-pixel work
 // ---------------------------------------------------------------------------
@@ -794,43 +783,44 @@ __device__ __forceinline__ void wait_vmem() {
 // among them); the first of them ends with the sums.  A power of two of parts:
 // lane q has parts q, q + lanes, ..., and the lanes' tree is even.  Else that tree
 // would be lopsided, and its error that of up to log2(n) additions of nearly the
-// whole (3000^2/300 in five parts: the sums' rms error 12% above that of one
-// workgroup): a quarter to a half as many lanes, two to four parts each, in FP64.
+// whole: a quarter to a half as many lanes, two to four parts each.  Up to sixteen
+// parts are added in FP64, because the parts' own waves have left roundoff too
+// (3000^2/300 in five parts: rms error of Sx 0.75 units of roundoff as a plain
+// tree, 0.58 so, 0.69 in one workgroup; sixteen or more FP64 parts are too slow:
+// 1536^2/768 in 96 parts 7.4 us as a plain tree, 7.9 in FP64, 7.4 compensated).
+constexpr int kExactParts = 16;
+
 template <int MODE, typename Part>
 __device__ __forceinline__ Sum4 parts_sum(int n, int log_g, int q, Part part) {
     const int log_n = 31 - __clz(n);
-    if (n == 1 << log_n) {
-        Acc c = acc_zero();
-        for (int p = q; p < n; p += 1 << log_g) {
-            const float4 w = part(p);
-            if constexpr ((MODE & kLisi) != 0) cadd(c.A, w.x);
-            if constexpr ((MODE & kAug) != 0) cadd(c.P, w.y);
-            cadd(c.X, w.z);
-            cadd(c.Y, w.w);
-        }
-        return group_allreduce<MODE>(fold(c), min(log_g, log_n));
-    }
-    const int log_l = min(log_g, log_n - 1), lanes = 1 << log_l;
+    const bool even = n == 1 << log_n;
+    const int log_l = min(log_g, even ? log_n : log_n - 1), lanes = 1 << log_l;
+    const bool exact = !even && n < kExactParts;
+    Acc c = acc_zero();
     Sum4d d{0.0, 0.0, 0.0, 0.0};
     for (int from = q; q < lanes && from < n; from += 4 * lanes) {
-        float4 w[4];   // loads in flight
+        float4 w[4];   // loads in flight, none behind a branch that would wait for one
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            w[i] = from + i * lanes < n ? part(from + i * lanes) : float4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < 4; ++i) w[i] = part(min(from + i * lanes, n - 1));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if constexpr ((MODE & kLisi) != 0) d.A += w[i].x;
-            if constexpr ((MODE & kAug) != 0) d.P += w[i].y;
-            d.X += w[i].z;
-            d.Y += w[i].w;
+            if (from + i * lanes >= n) break;
+            if (exact) {
+                if constexpr ((MODE & kLisi) != 0) d.A += w[i].x;
+                if constexpr ((MODE & kAug) != 0) d.P += w[i].y;
+                d.X += w[i].z;
+                d.Y += w[i].w;
+            } else {
+                if constexpr ((MODE & kLisi) != 0) cadd(c.A, w[i].x);
+                if constexpr ((MODE & kAug) != 0) cadd(c.P, w[i].y);
+                cadd(c.X, w[i].z);
+                cadd(c.Y, w[i].w);
+            }
         }
     }
-    if (log_l > 0) lanes_add<MODE, 0xB1>(d);
+    if (!exact) return group_allreduce<MODE>(fold(c), log_l);
+    if (log_l > 0) lanes_add<MODE, 0xB1>(d);   // at most four lanes
     if (log_l > 1) lanes_add<MODE, 0x4E>(d);
-    if (log_l > 2) lanes_add<MODE, 0x141>(d);
-    if (log_l > 3) lanes_add<MODE, 0x140>(d);
-    if (log_l > 4) lanes_swap_add<MODE, 16>(d);
-    if (log_l > 5) lanes_swap_add<MODE, 32>(d);
     return Sum4{(float)d.A, (float)d.P, (float)d.X, (float)d.Y};
 }
 
@@ -847,8 +837,8 @@ __device__ __forceinline__ void combine_parts(const KArgs &a, int grp, int lane)
     const int j = lane >> a.log_grp;   // the lane group's tile
     const int q = lane & ((1 << a.log_grp) - 1);
     const int tx = txg * tiles_per_wave(a) + j;
+    // (A tile past the image's last has places for its parts too; its sums go nowhere.)
     const Sum4 s = parts_sum<MODE>(a.ks, a.log_grp, q, [&](int p) {
-        if (tx >= a.ns) return float4{0.f, 0.f, 0.f, 0.f};
         const float4 *src = ws + (base + p) * pitch + j;
         return COHERENT ? load_coherent(src) : *src;
     });
