@@ -1532,11 +1532,10 @@ LaunchFn pick_unroll(int unroll, const Want &w) {
 }
 
 // The instantiated launch shapes: waves 1/2/4/8 with unroll 4/8 and waves 16
-// with unroll 4 for vec 4, and waves 1/4 with unroll 4 for vec 2 and vec 1;
-// each with and without a row split across workgroups.  vec 2 and vec 1 run
-// the any-address quad kernel for NT >= 4, four waves per workgroup whichever
-// is asked for (an odd NT could only ask for one), and the narrow loads below
-// that.
+// with unroll 4 for vec 4; for vec 2 and vec 1 with unroll 4 the any-address quad
+// kernel for NT >= 4, four waves per workgroup whether one or four are asked for
+// (an odd NT could only ask for one), and one wave of narrow loads below that.
+// Each with and without a row split across workgroups.
 // Timeline launches exist for the vec 4 shapes, fused mode.
 LaunchFn pick(const iqa_launch_cfg &c, const Want &w) {
     if (c.vec == 4) {
@@ -1551,9 +1550,8 @@ LaunchFn pick(const iqa_launch_cfg &c, const Want &w) {
     }
     if (w.tl || c.unroll != 4 || !(c.waves == 1 || c.waves == 4)) return nullptr;
     if (w.any) return pick_shape<4, true, kAnyWaves, 4>(w);
-    if (c.vec == 2) return c.waves == 1 ? pick_shape<2, false, 1, 4>(w) : pick_shape<2, false, 4, 4>(w);
-    if (c.vec == 1) return c.waves == 1 ? pick_shape<1, false, 1, 4>(w) : pick_shape<1, false, 4, 4>(w);
-    return nullptr;
+    if (c.waves != 1) return nullptr;
+    return c.vec == 2 ? pick_shape<2, false, 1, 4>(w) : pick_shape<1, false, 1, 4>(w);
 }
 
 bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
