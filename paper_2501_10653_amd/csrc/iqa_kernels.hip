@@ -1623,10 +1623,14 @@ iqa_status geometry(int64_t N, int64_t NT, const iqa_launch_cfg &c, Geometry &g)
 // tile row is whole 128-byte lines (3840^2/96: 21.0, one row of two tiles
 // 23.3), else one row of two tiles, which share the line between them
 // (3840^2/120: 20.6, two rows above 22).  Any-address quads: 6 items for rows
-// of at most 8 quads (8190^2/30: 4 items 80.0, 8 items 84.0), 16 for rows that
-// nearly fill 16 lanes (2000^2/50: 13 items 8.1, 7 items 8.6; 2025^2/45, 12
-// quads: 6 items 8.5, 12 items 9.7), and two rows at 32 lanes (8190^2/90: 85.8
-// and 88.2).
+// of at most 8 quads (8190^2/30: 4 items 80.0, 8 items 84.0), and two rows at 32
+// lanes (8190^2/90: 85.8 and 88.2).  Rows of 13 to 16 quads keep 16 lanes, up to
+// 16 items, where that makes one workgroup per CU or 1.5 to 2 (16 lanes and 32: 256
+// of them, 1600^2/50 6.1 and 6.3; 400, 2000^2/50 7.7 and 8.3; 462, 2394^2/57 9.5 and 10.2; 484, 2508^2/57 9.9 and
+// 10.4, 2772^2/63 11.7 and 11.7; but 315, 2135^2/61 9.7 and 9.0; 564, 2350^2/50
+// 10.2 and 9.8; 540, 2385^2/53 11.1 and 10.4, 2835^2/63 14.5 and 13.2; 1600,
+// 4000^2/50 21.5 and 20.7); 9 to 12 quads do not (484, 1804^2/41 7.2 and 7.0,
+// 1980^2/45 7.8 and 7.7; 540, 2025^2/45 9.4 and 8.4).
 //
 // Eight waves per workgroup instead of four, unsplit, where there is a workgroup
 // for more than half of the CUs and at most one for each, from 16 items per lane
@@ -1672,7 +1676,8 @@ iqa_launch_cfg default_cfg(int64_t N, int64_t NT, const float *x, const float *y
     };
     while (lanes < kWave) {
         const bool few = workgroups() * wg_waves < 1024;
-        const int64_t most = !any ? 8 : row_lanes <= 8 ? 6 : 16 * cols >= 13 * row_lanes ? 16 : 8;
+        const bool rounds = workgroups() <= 256 || (workgroups() > 384 && workgroups() <= 512);
+        const int64_t most = !any ? 8 : row_lanes <= 8 ? 6 : cols >= 13 && rounds ? 16 : 8;
         const bool long_lane = row_lanes <= 16 && items(rows) > most;
         const bool whole_lines = row_lanes == 32 && (any || NT % 32 == 0);
         if (!few && !long_lane && !whole_lines) break;
