@@ -75,8 +75,9 @@ def write_tuned_table(json_path: str = TUNED_JSON, inc_path: str = TUNED_INC) ->
             entries.append((N, NT, 2, cfg))
         waves = int(doc.get("batch_waves", 0))
     fields = ("vec", "waves", "unroll", "seg", "rp", "ksplit")
-    lines = ["// Generated by paper_2501_10653_amd/build.py from tuned/gfx950.json: the",
-             "// autotuner's measured-best launch shapes on gfx950.  Do not edit.",
+    lines = ["// Generated by paper_2501_10653_amd/build.py from tuned/gfx950.json: launch",
+             "// shapes by measurement on gfx950, the autotuner's and those of its `chosen`",
+             "// section.  Do not edit.",
              "static const TunedEntry kTuned[] = {"]
     for N, NT, kind, cfg in entries:
         vals = ", ".join(str(int(cfg[f])) for f in fields)

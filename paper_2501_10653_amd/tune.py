@@ -9,7 +9,10 @@ pool of distinct device copies of the pair (more bytes than the 256 MB
 Infinity Cache), so every launch streams from HBM.
 
 Results go to a JSON cache (``tuned/gfx950.json`` next to this file), which
-the build embeds into the library as its default shapes.
+the build embeds into the library as its default shapes.  Cells that were chosen
+by other measurements than these are kept in its ``chosen`` section, with the
+reason, and take the place of the tuner's in every run; the logs stay the
+tuner's own.
 
     python -m paper_2501_10653_amd.tune --sweep --batch --out paper_2501_10653_amd/tuned/gfx950.json
 """
@@ -279,6 +282,21 @@ def tune_serve(shapes: Sequence[Tuple[int, int]] = tuple(SERVE_SHAPES), K: int =
     return best, log_rows
 
 
+def keep_chosen(doc: dict) -> None:
+    """Put the cells of ``doc["chosen"]`` in the place of the tuner's."""
+    chosen = doc.get("chosen", {})
+    for key, cell in chosen.get("single", {}).items():
+        rec = doc.setdefault("single", {}).setdefault(key, {})
+        if rec.get("cfg") != cell["cfg"]:
+            rec.clear()     # the times are another shape's
+            rec["cfg"] = cell["cfg"]
+    for section in ("batch", "serve"):
+        for key, cell in chosen.get(section, {}).items():
+            doc.setdefault(section, {})[key] = cell["cfg"]
+    if "batch_waves" in chosen:
+        doc["batch_waves"] = chosen["batch_waves"]["value"]
+
+
 def load(path: str = DEFAULT_OUT) -> Optional[dict]:
     if not os.path.exists(path):
         return None
@@ -327,6 +345,7 @@ def main(argv=None) -> int:
         best, rows = tune_serve(log=log)
         doc["serve"] = best
         doc["serve_log"] = rows
+    keep_chosen(doc)
     doc["tuned_at_s"] = round(time.time() - t0, 1)
     os.makedirs(os.path.dirname(args.out), exist_ok=True)
     with open(args.out, "w") as fh:
