@@ -27,8 +27,9 @@
 //     current ones are reduced.
 //   * Every reduction has a fixed order and there are no floating-point
 //     atomics, so results are bitwise reproducible and bitwise symmetric in x, y.
-//   * augLISI = 1 - P/S is finalised in double-float so the subtraction keeps
-//     the accuracy of the sums.
+//   * LISI's quotient and augLISI = 1 - P/S are finalised in double-float: the
+//     one adds a single rounding, the other's subtraction keeps the accuracy of
+//     the sums.
 
 #include <hip/hip_runtime.h>
 
@@ -735,11 +736,11 @@ __device__ __forceinline__ void finish_group(const PairArgs &a, const float4 (&l
 // workgroups queue behind those round trips it is not, and the host picks
 // the combine launch (split_mode).
 //
-// Either way the partials are added the way the kernel adds pixels: lane q of
-// tile j's lane group Kahan-adds parts q, q + g, q + 2g, ... (g lanes per
-// tile), then the group is summed with the same fixed DPP tree.  The order
-// depends neither on the mechanism nor on which part came last, so results
-// are bitwise reproducible and equal between the two.
+// Either way the partials are added the way the kernel adds pixels: a lane of
+// tile j's lane group adds every so many of them with compensation, then the
+// group is summed with the same fixed DPP tree (parts_sum).  The order depends
+// neither on the mechanism nor on which part came last, so results are bitwise
+// reproducible and equal between the two.
 //
 // Workspace: partials [group][part][ht] float4 from a.ws on, and (ticket
 // mode) one 32-bit counter per group below a.ws (group g's at
@@ -1140,7 +1141,7 @@ __device__ __forceinline__ void batch_body(const BatchDesc *descs, int count, in
 }
 
 // The descriptor table in device memory (any number of pairs).  Bound by HBM: 30
-// ragged pairs (1.2 GB) run at 6.7 TB/s, 256 at 6.9, a plain read at 6.9.  Three
+// ragged pairs (1.2 GB) and 256 (10.8 GB) run at 6.7 TB/s, a plain read at 6.9.  Three
 // waves per SIMD: more waves with fewer loads each in flight are slower on mixed
 // batches (loads in batches of four, five waves: 223 us for the 30, 184 with eight).
 template <int U>
@@ -1246,9 +1247,8 @@ __global__ __launch_bounds__(kMergeThreads) void merge_small_kernel(MergeArgs m,
 // f above 16.  A parent's children are cut into `parts` runs of
 // part_children(), each added by kMergeThreads threads: a thread Kahan-adds
 // every kMergeThreads-th child of the run, with eight loads in flight, the lanes
-// and the four waves then add in a fixed order.  The runs' sums are added as
-// combine_parts adds a split tile's: lane by lane with Kahan compensation, then
-// over the wave.  (One run of any length took 393 us for the whole of a 512^2
+// and the four waves then add in a fixed order.  The runs' sums are added as a
+// split tile's parts are (parts_sum).  (One run of any length took 393 us for the whole of a 512^2
 // level, 4 MiB on one CU with one load in flight per thread.)
 __host__ __device__ __forceinline__ int64_t part_children(int64_t f, int64_t parts) {
     return ((f * f + parts - 1) / parts + kMergeThreads - 1) / kMergeThreads * kMergeThreads;
